@@ -82,6 +82,10 @@ __device__ __forceinline__ float2 c_mulc(float2 a, float2 b)  // a * conj(b)
 {
     return make_float2(fmaf(a.x, b.x, a.y * b.y), fmaf(a.y, b.x, -a.x * b.y));
 }
+__device__ __forceinline__ float2 c_mulc_add(float2 a, float2 b, float2 z)  // z + a * conj(b)
+{
+    return make_float2(fmaf(a.x, b.x, fmaf(a.y, b.y, z.x)), fmaf(a.y, b.x, fmaf(-a.x, b.y, z.y)));
+}
 
 // Two complex FP16 values of two transforms: (re.x + i im.x) and (re.y + i im.y).
 // A twiddle in this type carries the same value in both halves.
@@ -491,45 +495,60 @@ constexpr int kTwElems = kT1Elems + kT2Elems;
 // ---------------------------------------------------------------------------
 // Inverse: storage order in, natural order out (unnormalised).
 // PRUNE_OUT: only natural indices with k2b < 4 (i.e. < 1024) are produced.
+// TRIM: the twiddle tables lack their unit entries (k1 = 0, k2a = 0).
 // No scheduling barriers between its passes: the correlation kernels stay
 // within their register targets without them and run 2.5-3.6% faster (the
 // barriers around the callers' spectrum loads stay: without those the FP32
 // kernel took 1.7x as long).
-template <bool PRUNE_OUT, bool QUARTER = false, typename T>
+template <bool PRUNE_OUT, bool QUARTER = false, bool TRIM = false, bool TIGHT = false, typename T>
 __device__ __forceinline__ void ifft2048(T (&v)[32], T *xb, const T *t1, const T *t2, int l)
 {
+    auto tight = [] {
+        if constexpr (TIGHT) phase_barrier();
+    };
     dft16<true, 0>(v);
+    tight();
     dft16<true, 16>(v);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
-        for (int k1 = 1; k1 < 16; ++k1) v[16 * h + k1] = c_mul(v[16 * h + k1], t1[(16 * h + k1) * 64 + l]);
+        for (int k1 = 1; k1 < 16; ++k1) {
+            if (k1 % 4 == 1) tight();
+            v[16 * h + k1] = c_mul(v[16 * h + k1], t1[(16 * h + k1 - (TRIM ? h + 1 : 0)) * 64 + l]);
+        }
     }
+    tight();
     if constexpr (QUARTER)
         transpose_a_inv_q(v, xb, l);
     else
         transpose_a_inv(v, xb, l);
+    tight();
     dft16<true, 0>(v);
+    tight();
     dft16<true, 16>(v);
 #pragma unroll
     for (int k2a = 1; k2a < 16; ++k2a) {
-        const T w = t2[k2a * 8 + (l & 7)];
+        if (k2a % 4 == 1) tight();
+        const T w = t2[(k2a - (TRIM ? 1 : 0)) * 8 + (l & 7)];
         v[k2a] = c_mul(v[k2a], w);
         v[16 + k2a] = c_mul(v[16 + k2a], w);
     }
+    tight();
     if constexpr (QUARTER)
         transpose_b_inv_q(v, xb, l);
     else
         transpose_b_inv(v, xb, l);
+    tight();
     dft8<true, false, PRUNE_OUT, 0>(v);
     dft8<true, false, PRUNE_OUT, 8>(v);
+    tight();
     dft8<true, false, PRUNE_OUT, 16>(v);
     dft8<true, false, PRUNE_OUT, 24>(v);
 }
 
 // Forward: natural order in, storage order out.
 // PRUNE_IN: natural indices >= 1024 (k2b >= 4) are zero on input.
-template <bool PRUNE_IN, bool QUARTER = false, typename T>
+template <bool PRUNE_IN, bool QUARTER = false, bool TRIM = false, typename T>
 __device__ __forceinline__ void fft2048(T (&v)[32], T *xb, const T *t1, const T *t2, int l)
 {
     dft8<false, PRUNE_IN, false, 0>(v);
@@ -544,7 +563,7 @@ __device__ __forceinline__ void fft2048(T (&v)[32], T *xb, const T *t1, const T 
     phase_barrier();
 #pragma unroll
     for (int k2a = 1; k2a < 16; ++k2a) {
-        const T w = t2[k2a * 8 + (l & 7)];
+        const T w = t2[(k2a - (TRIM ? 1 : 0)) * 8 + (l & 7)];
         v[k2a] = c_mulc(v[k2a], w);
         v[16 + k2a] = c_mulc(v[16 + k2a], w);
     }
@@ -560,7 +579,8 @@ __device__ __forceinline__ void fft2048(T (&v)[32], T *xb, const T *t1, const T 
     for (int h = 0; h < 2; ++h) {
         phase_barrier();
 #pragma unroll
-        for (int k1 = 1; k1 < 16; ++k1) v[16 * h + k1] = c_mulc(v[16 * h + k1], t1[(16 * h + k1) * 64 + l]);
+        for (int k1 = 1; k1 < 16; ++k1)
+            v[16 * h + k1] = c_mulc(v[16 * h + k1], t1[(16 * h + k1 - (TRIM ? h + 1 : 0)) * 64 + l]);
     }
     phase_barrier();
     dft16<false, 0>(v);

@@ -185,6 +185,7 @@ int make_plan(const gnss_request *r, gnss::Plan &p, bool need_outputs)
         return set_err(GNSS_ENOTSUP, "fs %lld Hz: more than %d samples per ms (and not k * 1.023 MHz, k <= %d)",
                        (long long)fs, gnss::kGenMaxN, gnss::kMaxSpc);
     p.gen_M = p.gen ? gnss::gen_transform_len((int)(fs / 1000)) : 0;
+    p.gen_seg = p.gen && gnss::gen_two_segments((int)(fs / 1000), p.gen_M) ? 1 : 0;
     p.fmt = r->fmt;
     p.n_samples = (int64_t)r->n;
     p.fs_hz = fs;
@@ -283,7 +284,8 @@ void build_batch(const gnss::Plan *plans, const gnss_request *reqs, int n, gnss:
     long long tot[gnss::kNumStages] = {};
     long long vec = 0, qk = 0, part = 0, grid_int = 0, fd_f2 = 0, gen_f2 = 0;
     B.gen_first = -1;
-    B.gen_pmask = 0;
+    B.gen_pmask = B.gen_rmask = 0;
+    B.gen_modes = 0;
     for (int r = 0; r < n; ++r) {
         const gnss::Plan &p = plans[r];
         gnss::ReqDesc &d = B.d[r];
@@ -308,8 +310,11 @@ void build_batch(const gnss::Plan *plans, const gnss_request *reqs, int n, gnss:
         if (p.gen) {
             d.gen = 1;
             d.gen_M = p.gen_M;
-            d.gen_P = std::min(p.gen_M, gnss::kGenLds);
-            B.gen_pmask |= (unsigned)d.gen_P;
+            d.gen_seg = p.gen_seg;
+            d.gen_P = p.gen_seg ? p.gen_M / 2 : std::min(p.gen_M, gnss::kGenLds);
+            d.gen_rows = gnss::gen_in_rows(d.gen_P, p.n_prn, p.n_dopp) ? 1 : 0;
+            (d.gen_rows ? B.gen_rmask : B.gen_pmask) |= (unsigned)d.gen_P;
+            B.gen_modes |= 1u << (d.gen_M == d.gen_P ? 1 : d.gen_seg ? 2 : 0);
             d.gen_x_off = gen_f2;
             d.gen_c_off = gen_f2 + (long long)p.n_dopp * p.Nnc * p.gen_M;
             gen_f2 += ((long long)p.n_dopp * p.Nnc + p.n_prn) * p.gen_M;
@@ -371,8 +376,8 @@ void build_batch(const gnss::Plan *plans, const gnss_request *reqs, int n, gnss:
             (long long)d.n_ptiles * cdiv(d.n_items, corr_w), p.detect ? (long long)p.n_prn * d.n_tau_blk : 0,
             p.detect ? (long long)p.n_prn : 0,
             fd_a, fd_b,
-            p.gen ? (long long)p.n_dopp * p.Nnc : 0, p.gen ? (long long)p.n_prn : 0,
-            p.gen ? (long long)p.n_prn * p.n_dopp : 0};
+            p.gen ? (p.n_prn + (long long)p.n_dopp * p.Nnc) * (p.gen_seg ? 2 : 1) : 0,
+            p.gen ? cdiv(p.n_prn, d.gen_rows ? gnss::gen_group(d.gen_P) : 1) * p.n_dopp : 0};
         for (int st = 0; st < gnss::kNumStages; ++st) {
             B.pre[(size_t)st * (n + 1) + r] = tot[st];
             tot[st] += cnt[st];
@@ -506,6 +511,8 @@ int stage_batch(gnss_ctx *c, Workspace &w, BatchHost &B, hipStream_t s, gnss::La
     L.nav_pairs = c->nav_pairs;
     L.gen_off = B.gen_off;
     L.gen_pmask = B.gen_pmask;
+    L.gen_rmask = B.gen_rmask;
+    L.gen_modes = B.gen_modes;
     for (int st = 0; st < gnss::kNumStages; ++st) L.total[st] = B.total[st];
     return GNSS_OK;
 }

@@ -49,6 +49,7 @@ struct Plan {
     // length-N correlations run on zero-padded transforms of length gen_M
     int gen;
     int gen_M;      // power of two >= 2N
+    int gen_seg;    // 1: two segments on transforms of length gen_M / 2 (gen_two_segments)
     // a pass over part of the blocks (see ReqDesc): the first block, whether
     // the grid already holds earlier passes' sums, whether detection runs
     int b0 = 0, acc = 0, detect = 1;
@@ -72,6 +73,26 @@ inline int gen_transform_len(int N)
     int M = 64;
     while (M < 2 * N) M *= 2;
     return M;
+}
+
+// Two segments of the block on transforms of half the length (see the
+// general-rate kernels): each segment has at most gen_segment(N) samples, and
+// its correlation at N lags fits M / 2 points.  The shortest transform has 64.
+inline __host__ __device__ int gen_segment(int N) { return (N + 1) / 2; }
+inline bool gen_two_segments(int N, int M) { return M > N && M >= 128 && N + gen_segment(N) <= M / 2; }
+// PRNs per correlation workgroup at transform length P, in rows
+constexpr int gen_group(int P) { return P == 4096 ? 2 : 1; }
+// Whether a request's transforms of P points run as rows (see the
+// general-rate kernels).  At 4096 points a row workgroup does two of a CU's
+// six transforms with four waves, a one-piece one its CU's only transform
+// with sixteen: up to one item per CU the latter ends sooner (N = 2000, 10
+// blocks, 168 items: 88 us against 121), above that the former (1952 items:
+// 233 us against 406; 3872 items of 25 blocks: 0.79 ms against 1.81).  The
+// rule takes only the request's own sizes, so its results do not depend on
+// its batch.
+inline bool gen_in_rows(int P, int n_prn, int n_dopp)
+{
+    return P > 4096 || (P == 4096 && (long long)n_prn * n_dopp > 256);
 }
 
 // one-time tables
@@ -125,10 +146,9 @@ inline size_t g_bytes(long long n_vec, int precision)
 // requests (a single request is a batch of one); the correlation kernel can
 // run persistent, the others run one workgroup per work item
 // ---------------------------------------------------------------------------
-// kStGenX / kStGenC / kStGenCorr: the general-rate path (block spectra,
-// code spectra, correlation)
-enum Stage { kStBox = 0, kStVec, kStCorr, kStColmax, kStPeak, kStFdA, kStFdB, kStGenX, kStGenC, kStGenCorr,
-             kNumStages };
+// kStGenX / kStGenCorr: the general-rate path (code and block spectra,
+// correlation)
+enum Stage { kStBox = 0, kStVec, kStCorr, kStColmax, kStPeak, kStFdA, kStFdB, kStGenX, kStGenCorr, kNumStages };
 constexpr int kXcds = 8;
 
 // One request as the kernels see it (device memory).
@@ -165,10 +185,13 @@ struct ReqDesc {
     // accumulator, cycles * 2^64 per sample (phase of in-block sample n =
     // n * fd_dphase mod 2^64)
     unsigned long long fd_dphase;
-    // general rate: transform length M, its LDS part (M or M/2) and the
-    // request's block spectra [n_dopp][Nnc][M] and code spectra [n_prn][M]
-    // (float2 offsets in the general-rate region of the spectrum buffer)
-    int gen, gen_M, gen_P;
+    // general rate: spectrum length M, the length P of its transforms in LDS
+    // (M; M/2 with two segments, gen_seg, or for the even and odd bins of M =
+    // 32768) and the request's block spectra [n_dopp][Nnc][M] and code spectra
+    // [n_prn][M] (float2 offsets in the general-rate region of the spectrum
+    // buffer)
+    int gen, gen_M, gen_P, gen_seg;
+    int gen_rows;         // 1: the transforms run as rows of 2048 points (gen_in_rows)
     long long gen_x_off, gen_c_off;
     // A long request may run in passes over its blocks: this pass's blocks
     // are the record's blocks b0 .. b0 + Nnc - 1 (sample positions and
@@ -201,7 +224,8 @@ struct Launch {
     int fd;                       // 1: frequency-domain Doppler (exact-length contexts)
     int nav_pairs;                // 1: navigation-bit hypotheses (exact-length contexts)
     size_t gen_off;               // bytes of the spectrum buffer before its general-rate region
-    unsigned gen_pmask;           // general-rate transform lengths P present (bit P)
+    unsigned gen_pmask, gen_rmask;  // general-rate transform lengths P present (bit P), in one piece and in rows
+    unsigned gen_modes;           // and modes: bit 1 M = P, bit 2 two segments, bit 0 even and odd bins
 };
 
 // Device-resident tables of a context.

@@ -1962,18 +1962,32 @@ __global__ __launch_bounds__(kSynthThreads) void k_fd_synth(const ReqDesc *__res
 //   R[tau] = sum_n f[n] c[(n - tau) mod N] = IDFT_M(DFT_M(f) conj(DFT_M(cc)))[M - N + tau] / M
 // (no wrap-around because M >= 2N).  When N is a power of two, M = N: the
 // same formula is then the N-point circular correlation itself (cc is one
-// period on [0, M)).  FP32 throughout, in every context
-// precision.  Each transform of P = min(M, 16384) points runs in one
-// workgroup's LDS; for M = 32768 the even and odd bins are two 16384-point
+// period on [0, M)).  FP32 throughout, in every context precision.
+//
+// Two segments.  Only N of the M outputs are lags, so a transform of half the
+// length is enough when the block is taken as two segments of at most P - N
+// samples (P = M/2): with f = f_0 + f_1, f_1 starting at sample n_1, and
+// cc_i[u] = c[(n_i + u) mod N] at [0, L + N), L = ceil(N/2),
+//   R[tau] = IDFT_P(sum_i DFT_P(f_i) conj(DFT_P(cc_i)))[P - N + tau] / P,
+// no wrap-around because L + N <= P.  The products are summed before the one
+// inverse, so a (PRN, bin, block) costs one P-point inverse instead of two or of
+// one twice as long,
+// and the two P-point spectra take the room of the M-point one.  Rule
+// (gen_two_segments): N + ceil(N/2) <= M/2, i.e. N in (2^k, 4/3 2^k]; three or
+// more segments would cover more lengths but need more room than the single
+// M-point spectrum.
+//
+// Each transform of P points runs in one workgroup's LDS.  Without segments
+// P = min(M, 16384); for M = 32768 the even and odd bins are two 16384-point
 // transforms:
 //   X[2k] = DFT_P(x[j] + x[j + P])[k],  X[2k + 1] = DFT_P((x[j] - x[j + P]) W_M^j)[k],
 // and the inverse's upper half (the only outputs needed, as N <= M/2) is
 //   out[P + k] = A[k] - W_M^-k B[k],  A = IDFT_P(Z even bins), B = IDFT_P(Z odd bins).
-// P <= 8192: in-place radix-8 passes and one radix-2 or 4 pass in a
+// P <= 2048: in-place radix-8 passes and one radix-2 or 4 pass in a
 // 1024-thread workgroup, decimation in frequency forward (natural order in,
 // digit-reversed out) and the exact adjoint inverse (digit-reversed in,
 // natural out), so spectra are multiplied in the order they are stored.
-// P = 16384: four-step 8 x 2048 transforms (below).
+// P = 4096 to 16384: four-step P/2048 x 2048 transforms (below).
 // ===========================================================================
 
 // Radix of the LDS passes (a radix-16 butterfly with its twiddles needs about
@@ -2135,161 +2149,124 @@ __device__ __forceinline__ int opaque_tid()
     return t;
 }
 
-// The general-rate kernels are instantiated per transform length P < 16384
+// The general-rate kernels are instantiated per transform length P <= 2048
 // (LDS sized by P, so smaller transforms share a CU) and launched once for
 // each length present in a batch; items of requests with another length are
-// skipped.  P = 16384 has kernels of its own (below).
+// skipped.  The longer transforms have kernels of their own (below).
 
-// Code spectra of a general-rate request: item = (request, PRN).
-// CC[p][h P + i] = DFT_M(cc)[bin of storage position i of half h].
+// The chip floor(n 1023000 / fs) of sample n < N, fs = 1000 N: floor(1023 n / N),
+// in 32 bits (below 2^24) and already below 1023.
+__device__ __forceinline__ int gen_chip(int n, int N) { return (int)((unsigned)n * (unsigned)kCodeLen / (unsigned)N); }
+
+// The spectra of a general-rate request, one launch for both kinds so that
+// neither waits for the other: an item is one segment of a PRN's code
+// (n_prn of them, first) or of a (Doppler bin, block).
+// Code: CC[p][h P + i] = DFT_P(cc_h)[bin of storage position i], cc_h[j] =
+// c[(n_h + j) mod N] for j below the segment's length + N, else 0 (one
+// segment: c[j mod N] for j < 2N).
+// Block: the carrier NCO, first mixing stage and fold (the integer
+// arithmetic of the polyphase path), delayed circularly by the code-Doppler
+// shift if any, then the zero-padded forward transform.
 template <int P>
-__global__ __launch_bounds__(kGenThreads) void k_gen_code(const ReqDesc *__restrict__ R, const BatchHdr *H,
+__global__ __launch_bounds__(kGenThreads) void k_gen_spec(const ReqDesc *__restrict__ R, const BatchHdr *H,
                                                           const long long *pre, const uint8_t *codes,
-                                                          const float2 *tw, float2 *gen)
-{
-    __shared__ float2 x[P + P / 32];
-    __shared__ float2 s_tw[P / kGenRad];
-    const int n_req = H->n_req;
-    const long long total = H->total[kStGenC];
-    const long long *pst = pre + (long long)kStGenC * (n_req + 1);
-    for (long long it = blockIdx.x; it < total; it += gridDim.x) {
-        const int r = find_req(pst, n_req, it);
-        const ReqDesc &d = R[r];
-        if (d.gen_P != P) continue;
-        const int pi = (int)(it - pst[r]);
-        const uint8_t *code = codes + (long long)d.prns[pi] * kCodeLen;
-        const int N = d.N, M = d.gen_M;
-        const long long fs = (long long)N * 1000;
-        float2 *dst = gen + d.gen_c_off + (long long)pi * M;
-        // c[j mod N] for j < 2N, else 0
-        auto cc = [&](int j) -> float {
-            if (j >= 2 * N) return 0.f;
-            const long long n = j >= N ? j - N : j;
-            return code[(n * 1023000LL / fs) % kCodeLen] ? -1.f : 1.f;
-        };
-        for (int h = 0; h < M / P; ++h) {
-            __syncthreads();  // the previous transform's outputs are read
-            if (h == 0) gen_load_tw(s_tw, P, tw);
-            for (int j = threadIdx.x; j < P; j += kGenThreads) {
-                float2 v;
-                if (M == P) {
-                    v = make_float2(cc(j), 0.f);
-                } else if (h == 0) {
-                    v = make_float2(cc(j) + cc(j + P), 0.f);
-                } else {
-                    const float c = cc(j) - cc(j + P);
-                    const float2 w = tw[j];  // W_M^j, M = 32768
-                    v = make_float2(c * w.x, c * w.y);
-                }
-                x[gx(j)] = v;
-            }
-            __syncthreads();
-            gen_forward<P>(x, s_tw);
-            for (int j = threadIdx.x; j < P; j += kGenThreads) dst[(long long)h * P + j] = x[gx(j)];
-        }
-    }
-}
-
-// Block spectra of a general-rate request: item = (request, Doppler bin,
-// block).  The carrier NCO, first mixing stage and fold of the block (the
-// integer arithmetic of the polyphase path), delayed circularly by the
-// code-Doppler shift if any, then the zero-padded forward transform.
-template <int P>
-__global__ __launch_bounds__(kGenThreads) void k_gen_x(const ReqDesc *__restrict__ R, const BatchHdr *H,
-                                                       const long long *pre, const uint32_t *lut, const float2 *tw,
-                                                       float2 *gen)
+                                                          const uint32_t *lut, const float2 *tw, float2 *gen)
 {
     __shared__ float2 x[P + P / 32];
     __shared__ float2 s_tw[P / kGenRad];
     __shared__ uint32_t s_lut[1024];
-    constexpr int kPer = kGenMaxN / kGenThreads;
     for (int i = threadIdx.x; i < 1024; i += kGenThreads) s_lut[i] = lut[i];
+    gen_load_tw(s_tw, P, tw);
     const int n_req = H->n_req;
     const long long total = H->total[kStGenX];
     const long long *pst = pre + (long long)kStGenX * (n_req + 1);
     for (long long it = blockIdx.x; it < total; it += gridDim.x) {
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
-        if (d.gen_P != P) continue;
-        const long long local = it - pst[r];
-        const int k = (int)(local / d.Nnc), b = (int)(local % d.Nnc);
+        if (d.gen_P != P || d.gen_rows) continue;
         const int N = d.N, M = d.gen_M;
-        const uint32_t D = d.dk[k];
-        const int shift = d.cshift ? d.cshift[(long long)k * d.Nnc + b] : 0;
-        __syncthreads();  // s_lut staged; the previous item's reads of x and s_tw are done
-        gen_load_tw(s_tw, P, tw);
-        // the folded block, n = tid + 1024 i (zero at n >= N)
-        float2 f[kPer];
-        int tid = opaque_tid();
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) {
-            const int n = tid + kGenThreads * i;
-            f[i] = make_float2(0.f, 0.f);
-            if (n < N) {
-                int m = n - shift;
-                if (m < 0) m += N;
-                const int2 v = wipe_fold_one(d.samples, d.fmt, N, d.Tc, s_lut, D, d.b0 + b, m);
-                f[i] = make_float2((float)v.x, (float)v.y);
-            }
-        }
-        float2 *dst = gen + d.gen_x_off + local * M;
-        for (int h = 0; h < M / P; ++h) {
-            if (h) __syncthreads();  // the previous half's outputs are read
-            tid = opaque_tid();
-#pragma unroll
-            for (int i = 0; i < kPer; ++i) {
-                const int n = tid + kGenThreads * i;
-                if (n < P) {
-                    // N <= P: the block has no samples at n + P; the odd-bin
-                    // half takes it times W_M^n
-                    float2 v = f[i];
-                    if (h == 1) v = c_mul(v, tw[n]);
-                    x[gx(n)] = v;
+        const int S = d.gen_seg ? 2 : 1, seg = d.gen_seg ? gen_segment(N) : N;
+        const long long local = it - pst[r];
+        const long long idx = local / S;
+        const int h = (int)(local - idx * S), n0 = h * seg;
+        float2 *dst;
+        __syncthreads();  // the tables are staged; the previous item's outputs are read
+        if (idx < d.n_prn) {
+            const uint8_t *code = codes + (long long)d.prns[idx] * kCodeLen;
+            dst = gen + d.gen_c_off + idx * M + h * P;
+            for (int j = threadIdx.x; j < P; j += kGenThreads) {
+                float v = 0.f;
+                if (j < seg + N) {
+                    int n = j + n0;  // below 2N
+                    if (n >= N) n -= N;
+                    v = code[gen_chip(n, N)] ? -1.f : 1.f;
                 }
+                x[gx(j)] = make_float2(v, 0.f);
             }
-            __syncthreads();
-            gen_forward<P>(x, s_tw);
-            for (int j = threadIdx.x; j < P; j += kGenThreads) dst[(long long)h * P + j] = x[gx(j)];
+        } else {
+            const int kb = (int)(idx - d.n_prn), k = kb / d.Nnc, b = kb - k * d.Nnc;
+            const uint32_t D = d.dk[k];
+            const int shift = d.cshift ? d.cshift[kb] : 0;
+            dst = gen + d.gen_x_off + (long long)kb * M + h * P;
+            // samples n0 .. n1 - 1 at [0, n1 - n0), zero above
+            const int n1 = min(N, n0 + seg);
+#pragma unroll 2
+            for (int j = threadIdx.x; j < P; j += kGenThreads) {
+                float2 f = make_float2(0.f, 0.f);
+                if (n0 + j < n1) {
+                    int m = n0 + j - shift;
+                    if (m < 0) m += N;
+                    const int2 v = wipe_fold_one(d.samples, d.fmt, N, d.Tc, s_lut, D, d.b0 + b, m);
+                    f = make_float2((float)v.x, (float)v.y);
+                }
+                x[gx(j)] = f;
+            }
         }
+        __syncthreads();
+        gen_forward<P>(x, s_tw);
+        for (int j = threadIdx.x; j < P; j += kGenThreads) dst[j] = x[gx(j)];
     }
 }
 
-// One correlation item of length P = M (see k_gen_corr).
+// One correlation item of length P <= 2048 (see k_gen_corr).
 template <int P>
 __device__ __forceinline__ void gen_corr_item(const ReqDesc &d, int k, int pi, const float2 *tw, const float2 *gen,
                                               float2 *x, float2 *s_tw)
 {
-    static_assert(P < kGenLds, "the 16384-point transforms have kernels of their own");
     constexpr int kPer = kGenMaxN / kGenThreads;
-    constexpr int kFill = 8;  // product values loaded per thread before they are stored
-    const int N = d.N;
-    const float2 *C = gen + d.gen_c_off + (long long)pi * P;
+    constexpr int kFill = (P + kGenThreads - 1) / kGenThreads;  // spectrum values per thread
+    const int N = d.N, M = d.gen_M;  // M = P, or 2 P: two segments
+    const float2 *C = gen + d.gen_c_off + (long long)pi * M;
     // 2^-24 (LUT scale) / P^2 (two unnormalised transforms), an exact power of two
     const float scale = ldexpf(1.f, -24 - 2 * (31 - __clz(P)));
     GNSS_GLOBAL float *row = gmem(d.grid) + ((long long)pi * d.n_dopp + k) * N;
     // fill x with the product of block b's spectrum and the code's; the first
     // loads are issued before the barrier that frees x
     auto product = [&](int b, bool first) {
-        const float2 *X = gen + d.gen_x_off + ((long long)k * d.Nnc + b) * P;
+        const float2 *X = gen + d.gen_x_off + ((long long)k * d.Nnc + b) * M;
         const int tid = opaque_tid();
-        for (int j0 = 0; j0 < P; j0 += kFill * kGenThreads) {
-            float2 xv[kFill], cv[kFill];
+        float2 xv[2][kFill], cv[2][kFill];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (h && M == P) break;
 #pragma unroll
             for (int u = 0; u < kFill; ++u) {
-                const int j = j0 + u * kGenThreads + tid;
+                const int j = u * kGenThreads + tid;
                 if (j < P) {
-                    xv[u] = X[j];
-                    cv[u] = C[j];
+                    xv[h][u] = X[h * P + j];
+                    cv[h][u] = C[h * P + j];
                 }
             }
-            if (j0 == 0) {
-                __syncthreads();  // the previous inverse's outputs are read
-                if (first) gen_load_tw(s_tw, P, tw);
-            }
+        }
+        __syncthreads();  // the previous inverse's outputs are read
+        if (first) gen_load_tw(s_tw, P, tw);
 #pragma unroll
-            for (int u = 0; u < kFill; ++u) {
-                const int j = j0 + u * kGenThreads + tid;
-                if (j < P) x[gx(j)] = c_mulc(xv[u], cv[u]);
+        for (int u = 0; u < kFill; ++u) {
+            const int j = u * kGenThreads + tid;
+            if (j < P) {
+                float2 z = c_mulc(xv[0][u], cv[0][u]);
+                if (M > P) z = c_mulc_add(xv[1][u], cv[1][u], z);  // the second segment's product on top
+                x[gx(j)] = z;
             }
         }
         __syncthreads();
@@ -2323,11 +2300,11 @@ __device__ __forceinline__ void gen_corr_item(const ReqDesc &d, int k, int pi, c
     }
 }
 
-// Correlation of a general-rate request with M = P <= 8192: item =
+// Correlation of a general-rate request with P <= 2048: item =
 // (request, Doppler bin, PRN), Doppler-major so that the workgroups running
-// together share the block spectra; over the blocks, Z = X conj(CC), the
-// inverse transform and |.|^2 of the lags' outputs, summed in block order
-// in registers; the grid gets sum |out|^2 2^-24 / M^2.
+// together share the block spectra; over the blocks, Z = X conj(CC) (summed
+// over the segments), the inverse transform and |.|^2 of the lags' outputs,
+// summed in block order in registers; the grid gets sum |out|^2 2^-24 / P^2.
 template <int P>
 __global__ __launch_bounds__(kGenThreads) void k_gen_corr(const ReqDesc *__restrict__ R, const BatchHdr *H,
                                                           const long long *pre, const float2 *tw,
@@ -2341,7 +2318,7 @@ __global__ __launch_bounds__(kGenThreads) void k_gen_corr(const ReqDesc *__restr
     for (long long it = blockIdx.x; it < total; it += gridDim.x) {
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
-        if (d.gen_P != P) continue;
+        if (d.gen_P != P || d.gen_rows) continue;
         const long long local = it - pst[r];
         const int k = (int)(local / d.n_prn), pi = (int)(local % d.n_prn);
         gen_corr_item<P>(d, k, pi, tw, gen, x, s_tw);
@@ -2364,6 +2341,16 @@ __device__ __forceinline__ float2 twiddle16(float2 v, int a, bool inv)
     }
 }
 
+// f(std::integral_constant<int, i>()) for i < N, in order
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void unrolled(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        unrolled<N, I + 1>(f);
+    }
+}
+
 // a copy the compiler cannot see through (keeps per-column products from
 // being hoisted out of loops and held)
 __device__ __forceinline__ float2 opaque(float2 v)
@@ -2373,196 +2360,216 @@ __device__ __forceinline__ float2 opaque(float2 v)
 }
 
 // ---------------------------------------------------------------------------
-// P = 16384: four-step transforms, 8 x 2048.  With n = 2048 a + b and
-// k = k1 + 8 k2 (a, k1 < 8; b, k2 < 2048)
-//   X[k1 + 8 k2] = DFT_2048 over b of ( W_P^(b k1) DFT_8 over a of x[2048 a + b] )[k2]:
-// a radix-8 stage across the eight 2048-point rows (in LDS, one column b per
+// P = 4096, 8192, 16384: four-step transforms, R x 2048 with R = P / 2048.
+// With n = 2048 a + b and k = k1 + R k2 (a, k1 < R; b, k2 < 2048)
+//   X[k1 + R k2] = DFT_2048 over b of ( W_P^(b k1) DFT_R over a of x[2048 a + b] )[k2]:
+// a radix-R stage across the R 2048-point rows (in LDS, one column b per
 // thread-iteration), then one 2048-point transform per wave (the register
 // FFT of the polyphase path, its transposes in the wave's own LDS row).  The
-// forward transform's rows end in the 2048-point storage order, so a half
-// spectrum is stored as [k1][1024 float4] exactly as that FFT leaves it; the
-// inverse is the adjoint (2048-point inverse per row, then conjugate
-// twiddles and the inverse radix-8 stage).  Two workgroup barriers per
+// forward transform's rows end in the 2048-point storage order, so a
+// P-point spectrum is stored as [k1][1024 float4] exactly as that FFT leaves
+// it; the inverse is the adjoint (2048-point inverse per row, then conjugate
+// twiddles and the inverse radix-R stage).  Two workgroup barriers per
 // transform instead of one per radix pass.
+//
+// What bounds the correlation is vector issue and, before that, the waits
+// between its phases (spectrum loads, LDS transposes, barriers), which other
+// waves have to fill.  So the rows meet the columns in two halves of 1024
+// columns each: a transform then needs 64 KB (P = 16384) or 32 KB of LDS for
+// its rows beside the 16 KB of twiddles, and two 8-wave workgroups (128
+// VGPRs, 8 of them spilled) or three 4-wave ones share a CU.  Measured, 32
+// PRNs x 121 bins x 25 blocks at 10 MHz: 3.7 ms, against 4.9 with whole rows
+// (148 KB, one workgroup per CU) and 7.84 with the two 16384-point inverses
+// per block that two segments replace (the whole search 8.42 -> 4.2 ms, the
+// vector work of the correlation 2.6 ms); 32 x 41 x 10 at 5 MHz: 0.62 -> 0.30
+// ms, where one 8192-point transform in radix-8 passes took 0.70.  A 4096-
+// point workgroup does two PRNs (one twiddle table for both).
 // ---------------------------------------------------------------------------
-constexpr int kG16Threads = 512;  // eight waves, one 2048-point row each
-constexpr int kG16Cols = kGenLds / 8 / kG16Threads;  // columns b per thread (4)
-static_assert(kGenLds == 8 * 2048, "four-step split of the 16384-point transform");
+constexpr int kRowMin = 4096;  // shortest transform done in rows
+template <int P>
+struct RowFft {
+    static constexpr int R = P / 2048;              // rows, one wave each
+    static constexpr int C = 32 / R;                // columns b per thread
+    static constexpr int T = 64 * R;                // threads of a transform
+    static constexpr int kGroups = gen_group(P);    // transforms per correlation workgroup
+    static constexpr int kSegRows = (P / 3 + 2047) / 2048;  // rows a segment's samples reach
+    static_assert(P >= kRowMin && P <= kGenLds && R * C == 32, "four-step lengths");
+};
 
-// Forward radix-8 stage: y[k1][b] = W_P^(b k1) sum_a x(2048 a + b) W_8^(a k1)
-// for this thread's columns b = tid + 512 j; x(j, a, b) supplies the input;
-// wb[j] = W_P^b (g16_bases).
-template <typename Src>
-__device__ __forceinline__ void g16_fwd_stage(float2 *y, const float2 (&wb)[kG16Cols], Src x)
+// The 2048-point twiddles without their unit entries (k1 = 0, k2a = 0), so
+// that two 80 KB workgroups share a CU's 160 KB.
+constexpr int kTrimT1 = 30 * 64, kTrimTw = kTrimT1 + 15 * 8;
+__device__ __forceinline__ void stage_twiddles_trim(float2 *s_tw, const float2 *tw, int tid, int nthreads)
 {
-    const int tid = opaque_tid();
+    for (int i = tid; i < kTrimTw; i += nthreads) {
+        int src = kT1Elems + 8 + (i - kTrimT1);
+        if (i < kTrimT1) src = i + 64 * (i < 15 * 64 ? 1 : 2);
+        s_tw[i] = tw[src];
+    }
+}
+
+// one column's W_P^(b k1), k1 = 1 .. R - 1, from w1 = W_P^b
+template <int R>
+__device__ __forceinline__ void row_powers(float2 (&w)[8], float2 w1)
+{
+    if constexpr (R == 8) {
+        gen_powers(w, w1);
+    } else {
+        w[1] = w1;
+        if constexpr (R == 4) {
+            w[2] = c_mul(w1, w1);
+            w[3] = c_mul(w[2], w1);
+        }
+    }
+}
+
+template <int R, bool INV>
+__device__ __forceinline__ void row_dft(float2 (&v)[R])
+{
+    if constexpr (R == 8) {
+        dft8<INV, false, false, 0>(v);
+    } else if constexpr (R == 4) {
+        dft4<INV>(v[0], v[1], v[2], v[3]);
+    } else {
+        const float2 a = v[0], b = v[1];
+        v[0] = c_add(a, b);
+        v[1] = c_sub(a, b);
+    }
+}
+
+// Forward radix-R stage: y[k1][b] = W_P^(b k1) sum_a x(2048 a + b) W_R^(a k1)
+// for this thread's columns b = tid + T j; x(j, a, b) supplies the input;
+// wb[j] = W_P^b (row_bases).
+template <int P, typename Src>
+__device__ __forceinline__ void row_fwd_stage(float2 *y, int t, const float2 (&wb)[RowFft<P>::C], Src x)
+{
+    constexpr int R = RowFft<P>::R;
 #pragma unroll
-    for (int j = 0; j < kG16Cols; ++j) {
-        const int b = tid + kG16Threads * j;
-        float2 v[8], w[8];
+    for (int j = 0; j < RowFft<P>::C; ++j) {
+        const int b = t + RowFft<P>::T * j;
+        float2 v[R], w[8];
 #pragma unroll
-        for (int a = 0; a < 8; ++a) v[a] = x(j, a, b);
-        dft8<false, false, false, 0>(v);
-        gen_powers(w, opaque(wb[j]));  // formed here, not hoisted and held
+        for (int a = 0; a < R; ++a) v[a] = x(j, a, b);
+        row_dft<R, false>(v);
+        row_powers<R>(w, opaque(wb[j]));  // formed here, not hoisted and held
 #pragma unroll
-        for (int r = 1; r < 8; ++r) v[r] = c_mul(v[r], w[r]);
+        for (int r = 1; r < R; ++r) v[r] = c_mul(v[r], w[r]);
 #pragma unroll
-        for (int k1 = 0; k1 < 8; ++k1) y[k1 * 2048 + b] = v[k1];
+        for (int k1 = 0; k1 < R; ++k1) y[k1 * 2048 + b] = v[k1];
         phase_barrier();  // one column at a time (registers)
     }
 }
 
 // W_P^b of this thread's columns b, from the table of W_32768^i (loaded once
-// per kernel: the stages' column loop would otherwise wait for each); with
-// wm, W_M^b for M = 2P = 32768, which gives W_M^(2048 a + b) = W_M^b W_16^a.
-__device__ __forceinline__ void g16_bases(float2 (&wb)[kG16Cols], float2 (&wm)[kG16Cols], const float2 *twg)
+// per kernel: the stages' column loop would otherwise wait for each)
+template <int P>
+__device__ __forceinline__ void row_bases(float2 (&wb)[RowFft<P>::C], int t, const float2 *twg)
 {
 #pragma unroll
-    for (int j = 0; j < kG16Cols; ++j) {
-        wb[j] = twg[2 * (threadIdx.x + kG16Threads * j)];
-        wm[j] = twg[threadIdx.x + kG16Threads * j];
-    }
+    for (int j = 0; j < RowFft<P>::C; ++j) wb[j] = twg[(kGenTwLen / P) * (t + RowFft<P>::T * j)];
 }
 
 // Wave k1 transforms row k1 of y (natural order) and stores the storage-order
 // result at dst[k1][1024 float4].  The row is the wave's transpose buffer.
-__device__ __forceinline__ void g16_fwd_rows(float2 *y, const float2 *s_tw, float4 *dst)
+__device__ __forceinline__ void row_fwd_rows(float2 *y, int t, const float2 *s_tw, float4 *dst)
 {
-    const int tid = opaque_tid(), w = tid >> 6, l = tid & 63;
+    const int w = t >> 6, l = t & 63;
     float2 *row = y + w * 2048;
     float2 v[32];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
         for (int k2b = 0; k2b < 8; ++k2b) v[8 * u + k2b] = row[l + 64 * u + 256 * k2b];
-    fft2048<false, true>(v, row, s_tw, s_tw + kT1Elems, l);
+    fft2048<false, true, true>(v, row, s_tw, s_tw + kTrimT1, l);
     float4 *d = dst + w * 1024;
 #pragma unroll
     for (int jj = 0; jj < 16; ++jj)
         d[jj * 64 + l] = make_float4(v[2 * jj].x, v[2 * jj].y, v[2 * jj + 1].x, v[2 * jj + 1].y);
 }
 
-// Wave k1 forms row k1 of X conj(C) (half spectra in the stored layout),
-// transforms it back and leaves the natural-order row in y.  The barrier
-// that frees y (the previous stage's reads) is taken inside, after the
-// spectra are loaded, so their latency overlaps the wait.
-__device__ __forceinline__ void g16_inv_rows(float2 *y, const float2 *s_tw, const float4 *X, const float4 *C)
+// Registers 2 jj, 2 jj + 1 of row k1 of X conj(C), J0 <= jj < J0 + NJ (spectra in
+// the stored layout); with SEGS = 2 the sum of the two segments' products, the
+// second segment P/2 float4 on.  X and C point at this lane of its row.
+template <int P, int SEGS, int J0, int NJ>
+__device__ __forceinline__ void row_product(float2 (&z)[32], const float4 *X, const float4 *C)
 {
-    // an opaque index, so that no address is hoisted out of the callers' loops
-    const int tid = opaque_tid(), w = tid >> 6, l = tid & 63;
-    float2 *row = y + w * 2048;
-    const float4 *xq = X + w * 1024, *cq = C + w * 1024;
-    float2 z[32];
-    phase_barrier();
+    float4 x[SEGS][NJ], c[SEGS][NJ];
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
-        const float4 t = xq[jj * 64 + l], c = cq[jj * 64 + l];
-        z[2 * jj] = c_mulc(make_float2(t.x, t.y), make_float2(c.x, c.y));
-        z[2 * jj + 1] = c_mulc(make_float2(t.z, t.w), make_float2(c.z, c.w));
+    for (int i = 0; i < SEGS; ++i)
+#pragma unroll
+        for (int q = 0; q < NJ; ++q) {
+            x[i][q] = X[i * (P / 2) + (J0 + q) * 64];
+            c[i][q] = C[i * (P / 2) + (J0 + q) * 64];
+        }
+#pragma unroll
+    for (int q = 0; q < NJ; ++q) {
+        float2 &z0 = z[2 * (J0 + q)], &z1 = z[2 * (J0 + q) + 1];
+        z0 = c_mulc(make_float2(x[0][q].x, x[0][q].y), make_float2(c[0][q].x, c[0][q].y));
+        z1 = c_mulc(make_float2(x[0][q].z, x[0][q].w), make_float2(c[0][q].z, c[0][q].w));
+        if constexpr (SEGS == 2) {
+            z0 = c_mulc_add(make_float2(x[1][q].x, x[1][q].y), make_float2(c[1][q].x, c[1][q].y), z0);
+            z1 = c_mulc_add(make_float2(x[1][q].z, x[1][q].w), make_float2(c[1][q].z, c[1][q].w), z1);
+        }
     }
-    __syncthreads();
-    ifft2048<false, true>(z, row, s_tw, s_tw + kT1Elems, l);
+}
+
+// Wave k1 transforms its row z back and leaves the natural-order row in y.
+__device__ __forceinline__ void row_inv_rows(float2 (&z)[32], float2 *y, int t, const float2 *s_tw)
+{
+    const int w = t >> 6, l = t & 63;
+    float2 *row = y + w * 2048;
+    ifft2048<false, true, true>(z, row, s_tw, s_tw + kTrimT1, l);
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
         for (int k2b = 0; k2b < 8; ++k2b) row[l + 64 * u + 256 * k2b] = z[8 * u + k2b];
 }
 
-// Inverse radix-8 stage: out(2048 a + b) = sum_k1 W_8^(-a k1) W_P^(-b k1) y[k1][b]
-// for this thread's columns; f(j, a, b, value) receives each output.
-template <typename Sink>
-__device__ __forceinline__ void g16_inv_stage(const float2 *y, const float2 (&wb)[kG16Cols], Sink f)
+// Column j of the inverse radix-R stage: v[a] = out(2048 a + b) =
+// sum_k1 W_R^(-a k1) W_P^(-b k1) y[k1][b], b = t + T j.  LEN: columns of y held
+// at a time (2048, or 1024: b mod 1024).
+template <int P, int LEN>
+__device__ __forceinline__ void row_inv_column(const float2 *y, int t, int j, float2 wb, float2 (&v)[RowFft<P>::R])
 {
-    const int tid = opaque_tid();
+    constexpr int R = RowFft<P>::R;
+    const int b = t + RowFft<P>::T * (j % (RowFft<P>::C * LEN / 2048));
+    float2 w[8];
 #pragma unroll
-    for (int j = 0; j < kG16Cols; ++j) {
-        const int b = tid + kG16Threads * j;
-        float2 v[8], w[8];
+    for (int k1 = 0; k1 < R; ++k1) v[k1] = y[k1 * LEN + b];
+    row_powers<R>(w, opaque(wb));  // formed here, not hoisted and held
 #pragma unroll
-        for (int k1 = 0; k1 < 8; ++k1) v[k1] = y[k1 * 2048 + b];
-        gen_powers(w, opaque(wb[j]));  // formed here, not hoisted and held
-#pragma unroll
-        for (int r = 1; r < 8; ++r) v[r] = c_mulc(v[r], w[r]);
-        dft8<true, false, false, 0>(v);
-#pragma unroll
-        for (int a = 0; a < 8; ++a) f(j, a, b, v[a]);
-        phase_barrier();  // one column at a time (registers)
-    }
+    for (int r = 1; r < R; ++r) v[r] = c_mulc(v[r], w[r]);
+    row_dft<R, true>(v);
 }
 
-// Code spectra, P = 16384 (see k_gen_code).
-__global__ __launch_bounds__(kG16Threads) void k_gen_code16(const ReqDesc *__restrict__ R, const BatchHdr *H,
-                                                            const long long *pre, const uint8_t *codes,
-                                                            const float2 *tw, const float2 *twg, float2 *gen)
+// The wipe-off and fold of this thread's samples n = n0 + 2048 a + t + T j
+// (a < NA, j < C) of block b (zero at n >= n1), delayed circularly by shift:
+// the arithmetic of wipe_fold_one with the milliseconds outermost, so that
+// the samples' loads of one millisecond are in flight together.
+template <int FMT, int P, int NA>
+__device__ __forceinline__ void row_fold_fmt(const ReqDesc &d, int b, uint32_t D, int shift, const uint32_t *s_lut,
+                                             int t, int n0, int n1, float2 (&f)[RowFft<P>::C][NA])
 {
-    constexpr int P = kGenLds;
-    __shared__ float2 y[P];
-    __shared__ float2 s_tw[kTwElems];
-    stage_twiddles(s_tw, tw, threadIdx.x, kG16Threads);
-    float2 wb[kG16Cols], wm[kG16Cols];
-    g16_bases(wb, wm, twg);
-    const int n_req = H->n_req;
-    const long long total = H->total[kStGenC];
-    const long long *pst = pre + (long long)kStGenC * (n_req + 1);
-    for (long long it = blockIdx.x; it < total; it += gridDim.x) {
-        const int r = find_req(pst, n_req, it);
-        const ReqDesc &d = R[r];
-        if (d.gen_P != P) continue;
-        const int pi = (int)(it - pst[r]);
-        const uint8_t *code = codes + (long long)d.prns[pi] * kCodeLen;
-        const int N = d.N, M = d.gen_M;
-        const long long fs = (long long)N * 1000;
-        float2 *dst = gen + d.gen_c_off + (long long)pi * M;
-        // c[j mod N] for j < 2N, else 0
-        auto cc = [&](int j) -> float {
-            if (j >= 2 * N) return 0.f;
-            const long long n = j >= N ? j - N : j;
-            return code[(n * 1023000LL / fs) % kCodeLen] ? -1.f : 1.f;
-        };
-        for (int h = 0; h < M / P; ++h) {
-            __syncthreads();  // the twiddles are staged; the previous rows are read
-            g16_fwd_stage(y, wb, [&](int j, int a, int b) -> float2 {
-                const int n = 2048 * a + b;
-                if (M == P) return make_float2(cc(n), 0.f);
-                if (h == 0) return make_float2(cc(n) + cc(n + P), 0.f);
-                // (cc[n] - cc[n + P]) W_M^n, M = 32768: W_M^b W_16^a
-                const float c = cc(n) - cc(n + P);
-                const float2 w = opaque(wm[j]);
-                return twiddle16(make_float2(c * w.x, c * w.y), a, false);
-            });
-            __syncthreads();
-            g16_fwd_rows(y, s_tw, (float4 *)(dst + (long long)h * P));
-        }
-    }
-}
-
-// The wipe-off and fold of this thread's 32 samples n = 2048 a + tid + 512 j
-// of block b (zero at n >= N), delayed circularly by shift: the arithmetic
-// of wipe_fold_one with the milliseconds outermost, so that the 32 samples'
-// loads of one millisecond are in flight together.
-template <int FMT>
-__device__ __forceinline__ void g16_fold(const ReqDesc &d, int b, uint32_t D, int shift, const uint32_t *s_lut,
-                                         int tid, float2 (&f)[kG16Cols][8])
-{
+    constexpr int C = RowFft<P>::C;
     const int N = d.N, Tc = d.Tc;
-    int yr[kG16Cols][8], yi[kG16Cols][8], m[kG16Cols][8];
+    int yr[C][NA], yi[C][NA], m[C][NA];
 #pragma unroll
-    for (int j = 0; j < kG16Cols; ++j)
+    for (int j = 0; j < C; ++j)
 #pragma unroll
-        for (int a = 0; a < 8; ++a) {
-            const int n = 2048 * a + tid + kG16Threads * j;
+        for (int a = 0; a < NA; ++a) {
+            const int n = n0 + 2048 * a + t + RowFft<P>::T * j;
             int mm = n - shift;
             if (mm < 0) mm += N;
-            m[j][a] = n < N ? mm : -1;
+            m[j][a] = n < n1 ? mm : -1;
             yr[j][a] = 0;
             yi[j][a] = 0;
         }
     for (int c = 0; c < Tc; ++c) {
         const long long base = (long long)((d.b0 + b) * Tc + c) * N;
 #pragma unroll
-        for (int j = 0; j < kG16Cols; ++j)
+        for (int j = 0; j < C; ++j)
 #pragma unroll
-            for (int a = 0; a < 8; ++a) {
+            for (int a = 0; a < NA; ++a) {
                 if (m[j][a] < 0) continue;
                 const long long ng = base + m[j][a];
                 int xr, xi;
@@ -2575,135 +2582,272 @@ __device__ __forceinline__ void g16_fold(const ReqDesc &d, int b, uint32_t D, in
             }
     }
 #pragma unroll
-    for (int j = 0; j < kG16Cols; ++j)
+    for (int j = 0; j < C; ++j)
 #pragma unroll
-        for (int a = 0; a < 8; ++a) f[j][a] = make_float2((float)yr[j][a], (float)yi[j][a]);
+        for (int a = 0; a < NA; ++a) f[j][a] = make_float2((float)yr[j][a], (float)yi[j][a]);
 }
 
-// Block spectra, P = 16384 (see k_gen_x).
-__global__ __launch_bounds__(kG16Threads) void k_gen_x16(const ReqDesc *__restrict__ R, const BatchHdr *H,
-                                                         const long long *pre, const uint32_t *lut,
-                                                         const float2 *tw, const float2 *twg, float2 *gen)
+template <int P, int NA>
+__device__ __forceinline__ void row_fold(const ReqDesc &d, int b, uint32_t D, int shift, const uint32_t *s_lut, int t,
+                                         int n0, int n1, float2 (&f)[RowFft<P>::C][NA])
 {
-    constexpr int P = kGenLds;
+    if (d.fmt == GNSS_CPLX_I8)
+        row_fold_fmt<GNSS_CPLX_I8, P, NA>(d, b, D, shift, s_lut, t, n0, n1, f);
+    else if (d.fmt == GNSS_REAL_I8)
+        row_fold_fmt<GNSS_REAL_I8, P, NA>(d, b, D, shift, s_lut, t, n0, n1, f);
+    else
+        row_fold_fmt<GNSS_REAL_2BIT_PACKED, P, NA>(d, b, D, shift, s_lut, t, n0, n1, f);
+}
+
+// Spectra in rows (see k_gen_spec).  The carrier table lies in the
+// transform's LDS, which the fold does not need yet.  M = 2 P without
+// segments (P = 16384): an item does the even and then the odd bins.
+template <int P>
+__global__ __launch_bounds__(RowFft<P>::T) void k_gen_spec_rows(const ReqDesc *__restrict__ R, const BatchHdr *H,
+                                                                const long long *pre, const uint8_t *codes,
+                                                                const uint32_t *lut, const float2 *tw,
+                                                                const float2 *twg, float2 *gen)
+{
+    using F = RowFft<P>;
+    constexpr int NS = F::kSegRows;
     __shared__ float2 y[P];
-    __shared__ float2 s_tw[kTwElems];
-    __shared__ uint32_t s_lut[1024];
-    for (int i = threadIdx.x; i < 1024; i += kG16Threads) s_lut[i] = lut[i];
-    stage_twiddles(s_tw, tw, threadIdx.x, kG16Threads);
-    float2 wb[kG16Cols], wm[kG16Cols];
-    g16_bases(wb, wm, twg);
+    __shared__ float2 s_tw[kTrimTw];
+    uint32_t *s_lut = (uint32_t *)y;
+    stage_twiddles_trim(s_tw, tw, threadIdx.x, F::T);
     const int n_req = H->n_req;
     const long long total = H->total[kStGenX];
     const long long *pst = pre + (long long)kStGenX * (n_req + 1);
     for (long long it = blockIdx.x; it < total; it += gridDim.x) {
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
-        if (d.gen_P != P) continue;
-        const long long local = it - pst[r];
-        const int k = (int)(local / d.Nnc), b = (int)(local % d.Nnc);
+        if (d.gen_P != P || !d.gen_rows) continue;
         const int N = d.N, M = d.gen_M;
-        const uint32_t D = d.dk[k];
-        const int shift = d.cshift ? d.cshift[(long long)k * d.Nnc + b] : 0;
-        __syncthreads();  // s_lut staged
-        // the folded block at n = 2048 a + tid + 512 j (zero at n >= N)
-        float2 f[kG16Cols][8];
-        const int tid = opaque_tid();
-        if (d.fmt == GNSS_CPLX_I8)
-            g16_fold<GNSS_CPLX_I8>(d, b, D, shift, s_lut, tid, f);
-        else if (d.fmt == GNSS_REAL_I8)
-            g16_fold<GNSS_REAL_I8>(d, b, D, shift, s_lut, tid, f);
-        else
-            g16_fold<GNSS_REAL_2BIT_PACKED>(d, b, D, shift, s_lut, tid, f);
-        float2 *dst = gen + d.gen_x_off + local * M;
-        for (int h = 0; h < M / P; ++h) {
-            if (h) __syncthreads();  // the previous half's rows are read
-            // N <= P: no samples at n + P; the odd-bin half takes x[n] W_M^n
-            g16_fwd_stage(y, wb, [&](int j, int a, int) -> float2 {
-                if (h == 0) return f[j][a];
-                // f W_M^n, n = 2048 a + b: W_M^b W_16^a
-                return twiddle16(c_mul(f[j][a], opaque(wm[j])), a, false);
+        const int S = d.gen_seg ? 2 : 1, seg = d.gen_seg ? gen_segment(N) : N;
+        const long long local = it - pst[r];
+        const long long idx = local / S;
+        const int h = (int)(local - idx * S), n0 = h * seg;
+        const bool halves = P == kGenLds && !d.gen_seg && M > P;
+        const int t = opaque_tid();
+        float2 f[F::C][F::R], wb[F::C];
+        float4 *dst;
+        __syncthreads();  // the previous item's rows are read
+        if (idx < d.n_prn) {
+            const uint8_t *code = codes + (long long)d.prns[idx] * kCodeLen;
+            auto cc = [&](int j) -> float {
+                if (j >= seg + N) return 0.f;
+                int n = j + n0;  // below 2N
+                if (n >= N) n -= N;
+                return code[gen_chip(n, N)] ? -1.f : 1.f;
+            };
+#pragma unroll
+            for (int j = 0; j < F::C; ++j)
+#pragma unroll
+                for (int a = 0; a < F::R; ++a) {
+                    // (x[n], x[n + P]) with two halves, else (x[n], 0): x is real
+                    const int n = 2048 * a + t + F::T * j;
+                    f[j][a] = make_float2(cc(n), halves ? cc(n + P) : 0.f);
+                }
+            dst = (float4 *)(gen + d.gen_c_off + idx * M) + h * (P / 2);
+        } else {
+            const int kb = (int)(idx - d.n_prn), k = kb / d.Nnc, b = kb - k * d.Nnc;
+            const uint32_t D = d.dk[k];
+            const int shift = d.cshift ? d.cshift[kb] : 0;
+            for (int i = threadIdx.x; i < 1024; i += F::T) s_lut[i] = lut[i];
+            __syncthreads();
+            if (d.gen_seg) {
+                // a segment has at most P/3 samples: rows a >= NS are zero
+                float2 g[F::C][NS];
+                row_fold<P, NS>(d, b, D, shift, s_lut, t, n0, min(N, n0 + seg), g);
+#pragma unroll
+                for (int j = 0; j < F::C; ++j)
+#pragma unroll
+                    for (int a = 0; a < F::R; ++a) f[j][a] = a < NS ? g[j][a < NS ? a : 0] : make_float2(0.f, 0.f);
+            } else {
+                // N <= M/2 (zeros above, so none at n + P), or N = M
+                row_fold<P, F::R>(d, b, D, shift, s_lut, t, 0, N, f);
+            }
+            dst = (float4 *)(gen + d.gen_x_off + (long long)kb * M) + h * (P / 2);
+            __syncthreads();  // the carrier table is read
+        }
+        row_bases<P>(wb, t, twg);
+        const bool two_reals = halves && idx < d.n_prn;
+        row_fwd_stage<P>(y, t, wb, [&](int j, int a, int) -> float2 {
+            return two_reals ? make_float2(f[j][a].x + f[j][a].y, 0.f) : f[j][a];
+        });
+        __syncthreads();
+        row_fwd_rows(y, t, s_tw, dst);
+        if (halves) {
+            // the odd bins: (x[n] - x[n + P]) W_M^n, n = 2048 a + b: W_M^b W_16^a
+            float2 wm[F::C];
+#pragma unroll
+            for (int j = 0; j < F::C; ++j) wm[j] = twg[t + F::T * j];
+            __syncthreads();  // the even bins' rows are read
+            row_fwd_stage<P>(y, t, wb, [&](int j, int a, int) -> float2 {
+                const float2 v = two_reals ? make_float2(f[j][a].x - f[j][a].y, 0.f) : f[j][a];
+                return twiddle16(c_mul(v, opaque(wm[j])), a, false);
             });
             __syncthreads();
-            g16_fwd_rows(y, s_tw, (float4 *)(dst + (long long)h * P));
+            row_fwd_rows(y, t, s_tw, dst + P / 2);
         }
     }
 }
 
-// Correlation, P = 16384 (see k_gen_corr): item = (request, Doppler bin,
-// PRN), Doppler-major; this thread's lags are the outputs n = 2048 a + b_j
-// at or above P - N, their sums in registers in groups of kSumGroup blocks
-// (for M = 2P with the first half's outputs A beside them).
-__global__ __launch_bounds__(kG16Threads) void k_gen_corr16(const ReqDesc *__restrict__ R, const BatchHdr *H,
-                                                            const long long *pre, const float2 *tw,
-                                                            const float2 *twg, const float2 *gen)
+// Correlation in rows (see k_gen_corr): item = (request, Doppler bin, group
+// of gen_group(P) PRNs, one transform each), Doppler-major; this thread's
+// lags are the outputs n = 2048 a + b_j at or above P - N, their sums in
+// registers in groups of kSumGroup blocks.  MODE 1, 2: one and two segments;
+// MODE 0 (P = 16384, M = 32768): two inverses, of the even and the odd bins,
+// the first one's outputs A kept beside the sums.  Requests of another length
+// or mode are skipped.
+template <int P, int MODE>
+__global__ __launch_bounds__(RowFft<P>::T *RowFft<P>::kGroups)
+    __attribute__((amdgpu_waves_per_eu(MODE == 0 ? 2 : P == kGenLds ? 4 : 3))) void k_gen_corr_rows(
+    const ReqDesc *__restrict__ R, const BatchHdr *H, const long long *pre, const float2 *tw, const float2 *twg,
+    const float2 *gen)
 {
-    constexpr int P = kGenLds;
-    __shared__ float2 y[P];
-    __shared__ float2 s_tw[kTwElems];
-    stage_twiddles(s_tw, tw, threadIdx.x, kG16Threads);
-    float2 wb[kG16Cols], wm[kG16Cols];
-    g16_bases(wb, wm, twg);
+    using F = RowFft<P>;
+    // one and two segments: the rows and columns meet in halves of 1024
+    // columns, so that more waves share a CU
+    constexpr int LEN = MODE == 0 ? 2048 : 1024;
+    __shared__ float2 ys[F::kGroups * F::R * LEN];
+    __shared__ float2 s_tw[kTrimTw];
+    stage_twiddles_trim(s_tw, tw, threadIdx.x, F::T * F::kGroups);
     const int n_req = H->n_req;
     const long long total = H->total[kStGenCorr];
     const long long *pst = pre + (long long)kStGenCorr * (n_req + 1);
     for (long long it = blockIdx.x; it < total; it += gridDim.x) {
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
-        if (d.gen_P != P) continue;
-        const long long local = it - pst[r];
-        const int k = (int)(local / d.n_prn), pi = (int)(local % d.n_prn);
         const int N = d.N, M = d.gen_M;
-        const float4 *C = (const float4 *)(gen + d.gen_c_off + (long long)pi * M);
-        const float scale = ldexpf(1.f, -24 - 2 * (31 - __clz(M)));
+        if (d.gen_P != P || !d.gen_rows || MODE != (M == P ? 1 : d.gen_seg ? 2 : 0)) continue;
+        const long long local = it - pst[r];
+        const int n_grp = (d.n_prn + F::kGroups - 1) / F::kGroups;
+        const int k = (int)(local / n_grp);
+        // the transform's threads t and PRN; a PRN past the list's end repeats the last one, unwritten
+        const int grp = __builtin_amdgcn_readfirstlane((int)threadIdx.x / F::T);
+        const int pl = (int)(local % n_grp) * F::kGroups + grp;
+        const bool written = pl < d.n_prn;
+        const int pi = written ? pl : d.n_prn - 1;
+        float2 *y = ys + grp * F::R * LEN;
+        const float scale = ldexpf(1.f, -24 - 2 * (31 - __clz(MODE ? P : 2 * P)));
         GNSS_GLOBAL float *row = gmem(d.grid) + ((long long)pi * d.n_dopp + k) * N;
-        // the sums in groups of kSumGroup blocks, each group's added to the
-        // row by the thread that holds it
+        const float4 *C0 = (const float4 *)(gen + d.gen_c_off + (long long)pi * M);
+        const float4 *X0 = (const float4 *)(gen + d.gen_x_off + (long long)k * d.Nnc * M);
+        // this lane of its row of block b's spectrum and of the code's (opaque,
+        // so that no address is hoisted out of the loops and held)
+        auto lane = [&](const float4 *base) {
+            const int t = opaque_tid() - grp * F::T;
+            return base + (t >> 6) * 1024 + (t & 63);
+        };
+        // the sums in groups of kSumGroup blocks, each group's added to the row
+        // by the thread that holds it
         for (int b0 = 0; b0 < d.Nnc; b0 += kSumGroup) {
-            float acc[kG16Cols][8];
+            float acc[F::C][F::R];
 #pragma unroll
-            for (int j = 0; j < kG16Cols; ++j)
+            for (int j = 0; j < F::C; ++j)
 #pragma unroll
-                for (int a = 0; a < 8; ++a) acc[j][a] = 0.f;
+                for (int a = 0; a < F::R; ++a) acc[j][a] = 0.f;
             const int b1 = min(d.Nnc, b0 + kSumGroup);
             for (int b = b0; b < b1; ++b) {
-                const float4 *X = (const float4 *)(gen + d.gen_x_off + ((long long)k * d.Nnc + b) * M);
-                // (the barrier inside: the twiddles are staged, the previous stage's reads of y done)
-                g16_inv_rows(y, s_tw, X, C);
-                __syncthreads();
-                if (M == P) {
-                    // lag tau = n - (P - N)
-                    g16_inv_stage(y, wb, [&](int j, int a, int bb, float2 o) {
-                        const int n = 2048 * a + bb;
-                        if (n >= P - N) acc[j][a] = fmaf(o.x, o.x, fmaf(o.y, o.y, acc[j][a]));
-                    });
+                const float4 *X = X0 + (long long)b * (M / 2);
+                float2 z[32];
+                if constexpr (MODE == 0) {
+                    row_product<P, 1, 0, 16>(z, lane(X), lane(C0));
                 } else {
-                    // lag tau is output P + kk, kk = n - (P - N): A - W_M^-kk B
-                    float2 A[kG16Cols][8];
-                    g16_inv_stage(y, wb, [&](int j, int a, int, float2 o) { A[j][a] = o; });
-                    g16_inv_rows(y, s_tw, X + P / 2, C + P / 2);
-                    __syncthreads();
-                    g16_inv_stage(y, wb, [&](int j, int a, int bb, float2 o) {
-                        const int n = 2048 * a + bb;
-                        if (n >= P - N) {
-                            // W_M^-n = conj(W_M^b) W_16^-a
-                            const float2 v = c_sub(A[j][a], twiddle16(c_mulc(o, opaque(wm[j])), a, true));
-                            acc[j][a] = fmaf(v.x, v.x, fmaf(v.y, v.y, acc[j][a]));
-                        }
+                    constexpr int NJ = P == kGenLds ? 2 : 4;
+                    const float4 *xl = lane(X), *cl = lane(C0);
+                    unrolled<16 / NJ>([&](auto jc) {
+                        row_product<P, MODE, decltype(jc)::value * NJ, NJ>(z, xl, cl);
+                        phase_barrier();
                     });
                 }
-            }
-            const int tid = opaque_tid();
+                __syncthreads();  // the twiddles are staged, the previous stage's reads of y done
+                int t = opaque_tid() - grp * F::T;
+                if constexpr (MODE != 0) {
+                    // the wave's transposes go through its own row of y, which its
+                    // half row of results then fills
+                    float2 *row_y = y + (t >> 6) * LEN;
+                    ifft2048<false, true, true, true>(z, row_y, s_tw, s_tw + kTrimT1, t & 63);
+                    auto half = [&](auto hc) {
+                        constexpr int h = decltype(hc)::value;
+                        // this half's W_P^b (needed after the barrier; held through the
+                        // transform they would not fit the registers)
+                        float2 wb[F::C / 2];
 #pragma unroll
-            for (int j = 0; j < kG16Cols; ++j)
+                        for (int jj = 0; jj < F::C / 2; ++jj)
+                            wb[jj] = twg[(kGenTwLen / P) * (t + F::T * (h * (F::C / 2) + jj))];
+                        if (h) __syncthreads();  // the first half's columns are read
 #pragma unroll
-                for (int a = 0; a < 8; ++a) {
-                    const int n = 2048 * a + tid + kG16Threads * j;
-                    if (n >= P - N) {
-                        GNSS_GLOBAL float *o = row + (n - (P - N));
-                        *o = (b0 || d.acc) ? *o + acc[j][a] * scale : acc[j][a] * scale;
+                        for (int u = 0; u < 4; ++u)
+#pragma unroll
+                            for (int k2b = 0; k2b < 4; ++k2b)
+                                row_y[(t & 63) + 64 * u + 256 * k2b] = z[8 * u + 4 * h + k2b];
+                        __syncthreads();
+                        // lag tau = n - (P - N)
+#pragma unroll
+                        for (int jj = 0; jj < F::C / 2; ++jj) {
+                            const int j = h * (F::C / 2) + jj;
+                            float2 v[F::R];
+                            row_inv_column<P, LEN>(y, t, j, wb[jj], v);
+#pragma unroll
+                            for (int a = 0; a < F::R; ++a) {
+                                const int n = 2048 * a + t + F::T * j;
+                                if (n >= P - N) acc[j][a] = fmaf(v[a].x, v[a].x, fmaf(v[a].y, v[a].y, acc[j][a]));
+                            }
+                            phase_barrier();  // one column at a time (registers)
+                        }
+                    };
+                    half(std::integral_constant<int, 0>());
+                    half(std::integral_constant<int, 1>());
+                } else {
+                    row_inv_rows(z, y, t, s_tw);
+                    __syncthreads();
+                    // lag tau is output P + kk, kk = n - (P - N): A - W_M^-kk B
+                    float2 A[F::C][F::R], wb[F::C], wm[F::C];
+                    row_bases<P>(wb, t, twg);
+#pragma unroll
+                    for (int j = 0; j < F::C; ++j) {
+                        row_inv_column<P, LEN>(y, t, j, wb[j], A[j]);
+                        phase_barrier();
+                    }
+                    row_product<P, 1, 0, 16>(z, lane(X + P / 2), lane(C0 + P / 2));
+                    __syncthreads();
+                    t = opaque_tid() - grp * F::T;
+                    row_inv_rows(z, y, t, s_tw);
+                    __syncthreads();
+                    t = opaque_tid() - grp * F::T;
+#pragma unroll
+                    for (int j = 0; j < F::C; ++j) wm[j] = twg[t + F::T * j];
+#pragma unroll
+                    for (int j = 0; j < F::C; ++j) {
+                        float2 v[F::R];
+                        row_inv_column<P, LEN>(y, t, j, wb[j], v);
+#pragma unroll
+                        for (int a = 0; a < F::R; ++a) {
+                            const int n = 2048 * a + t + F::T * j;
+                            if (n >= P - N) {
+                                // W_M^-n = conj(W_M^b) W_16^-a
+                                const float2 o = c_sub(A[j][a], twiddle16(c_mulc(v[a], opaque(wm[j])), a, true));
+                                acc[j][a] = fmaf(o.x, o.x, fmaf(o.y, o.y, acc[j][a]));
+                            }
+                        }
+                        phase_barrier();
                     }
                 }
+            }
+            const int t = opaque_tid() - grp * F::T;
+            if (written) {
+#pragma unroll
+                for (int j = 0; j < F::C; ++j)
+#pragma unroll
+                    for (int a = 0; a < F::R; ++a) {
+                        const int n = 2048 * a + t + F::T * j;
+                        if (n >= P - N) {
+                            GNSS_GLOBAL float *o = row + (n - (P - N));
+                            *o = (b0 || d.acc) ? *o + acc[j][a] * scale : acc[j][a] * scale;
+                        }
+                    }
+            }
         }
     }
 }
@@ -3033,40 +3177,56 @@ hipError_t launch_batch(const Launch &L, const Tables &T, int2 *d_F, void *d_G, 
         float2 *d_gen = (float2 *)((char *)d_G + L.gen_off);
         auto spectra = [&](auto pc) -> hipError_t {
             constexpr int P = decltype(pc)::value;
-            if constexpr (P == kGenLds) {
-                hipLaunchKernelGGL(k_gen_code16, dim3(grid_for(L.total[kStGenC], 65535, false)), dim3(kG16Threads),
-                                   0, s, L.reqs, L.hdr, L.pre, T.codes, T.tw, T.tw_gen, d_gen);
-                hipError_t e2 = hipGetLastError();
-                if (e2 != hipSuccess) return e2;
-                hipLaunchKernelGGL(k_gen_x16, dim3(grid_for(L.total[kStGenX], 65535, false)), dim3(kG16Threads), 0,
-                                   s, L.reqs, L.hdr, L.pre, d_lut, T.tw, T.tw_gen, d_gen);
-                return hipGetLastError();
-            } else {
-                hipLaunchKernelGGL(k_gen_code<P>, dim3(grid_for(L.total[kStGenC], 65535, false)), dim3(kGenThreads),
-                                   0, s, L.reqs, L.hdr, L.pre, T.codes, T.tw_gen, d_gen);
-                hipError_t e2 = hipGetLastError();
-                if (e2 != hipSuccess) return e2;
-                hipLaunchKernelGGL(k_gen_x<P>, dim3(grid_for(L.total[kStGenX], 65535, false)), dim3(kGenThreads), 0,
-                                   s, L.reqs, L.hdr, L.pre, d_lut, T.tw_gen, d_gen);
-                return hipGetLastError();
+            const unsigned wgs = grid_for(L.total[kStGenX], 65535, false);
+            if constexpr (P >= kRowMin) {
+                if (L.gen_rmask & (unsigned)P) {
+                    constexpr int kT = RowFft<P>::T;
+                    hipLaunchKernelGGL(k_gen_spec_rows<P>, dim3(wgs), dim3(kT), 0, s, L.reqs, L.hdr, L.pre, T.codes,
+                                       d_lut, T.tw, T.tw_gen, d_gen);
+                    const hipError_t e2 = hipGetLastError();
+                    if (e2 != hipSuccess) return e2;
+                }
             }
+            if constexpr (P <= kRowMin) {
+                if (L.gen_pmask & (unsigned)P)
+                    hipLaunchKernelGGL(k_gen_spec<P>, dim3(wgs), dim3(kGenThreads), 0, s, L.reqs, L.hdr, L.pre,
+                                       T.codes, d_lut, T.tw_gen, d_gen);
+            }
+            return hipGetLastError();
         };
-        if ((e = gen_lengths<64>(L.gen_pmask, spectra)) != hipSuccess) return e;
+        if ((e = gen_lengths<64>(L.gen_pmask | L.gen_rmask, spectra)) != hipSuccess) return e;
     }
     if ((e = mark(2)) != hipSuccess) return e;
     if (L.total[kStGenCorr] > 0) {
         const float2 *d_gen = (const float2 *)((char *)d_G + L.gen_off);
         auto corr = [&](auto pc) -> hipError_t {
             constexpr int P = decltype(pc)::value;
-            if constexpr (P == kGenLds)
-                hipLaunchKernelGGL(k_gen_corr16, dim3(grid_for(L.total[kStGenCorr], 65535, false)),
-                                   dim3(kG16Threads), 0, s, L.reqs, L.hdr, L.pre, T.tw, T.tw_gen, d_gen);
-            else
-                hipLaunchKernelGGL(k_gen_corr<P>, dim3(grid_for(L.total[kStGenCorr], 65535, false)),
-                                   dim3(kGenThreads), 0, s, L.reqs, L.hdr, L.pre, T.tw_gen, d_gen);
+            const unsigned wgs = grid_for(L.total[kStGenCorr], 65535, false);
+            if constexpr (P >= kRowMin) {
+                if (L.gen_rmask & (unsigned)P) {
+                    // one instance per mode present (see k_gen_corr_rows)
+                    auto rows = [&](auto kernel, int mode) -> hipError_t {
+                        if (!(L.gen_modes >> mode & 1)) return hipSuccess;
+                        hipLaunchKernelGGL(kernel, dim3(wgs), dim3(RowFft<P>::T * RowFft<P>::kGroups), 0, s, L.reqs,
+                                           L.hdr, L.pre, T.tw, T.tw_gen, d_gen);
+                        return hipGetLastError();
+                    };
+                    hipError_t e2 = rows(k_gen_corr_rows<P, 1>, 1);
+                    if (e2 == hipSuccess) e2 = rows(k_gen_corr_rows<P, 2>, 2);
+                    if constexpr (P == kGenLds) {
+                        if (e2 == hipSuccess) e2 = rows(k_gen_corr_rows<P, 0>, 0);
+                    }
+                    if (e2 != hipSuccess) return e2;
+                }
+            }
+            if constexpr (P <= kRowMin) {
+                if (L.gen_pmask & (unsigned)P)
+                    hipLaunchKernelGGL(k_gen_corr<P>, dim3(wgs), dim3(kGenThreads), 0, s, L.reqs, L.hdr, L.pre,
+                                       T.tw_gen, d_gen);
+            }
             return hipGetLastError();
         };
-        if ((e = gen_lengths<64>(L.gen_pmask, corr)) != hipSuccess) return e;
+        if ((e = gen_lengths<64>(L.gen_pmask | L.gen_rmask, corr)) != hipSuccess) return e;
     }
     if (L.total[kStCorr] > 0 && x) {
         // the frequency-domain variant wipes with unit exponentials (no LUT scale 2^12)
