@@ -284,6 +284,17 @@ __device__ __forceinline__ void lds_fence()
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 
+// Orders a wave's accesses to LDS that no other wave touches.  A wave's LDS
+// instructions execute in the order they are issued, so a write is seen by
+// the wave's later reads and a read is not overtaken by its later writes: only
+// the compiler has to keep the order.  It waits for a read's data where that
+// is used, so the rounds of an exchange overlap instead of draining one by one.
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    asm volatile("" ::: "memory");
+}
+
 // Keeps the machine scheduler from hoisting loads of a later phase above the
 // current one (which would raise register pressure past the occupancy target).
 __device__ __forceinline__ void phase_barrier()
@@ -303,11 +314,11 @@ __device__ __forceinline__ void transpose_a_inv(T (&v)[32], T *xb, int l)
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk) xb[kk * kStrideA + l + 64 * h] = v[16 * h + 8 * half + kk];
-        lds_fence();
+        wave_lds_order();
         const T *src = xb + (l >> 3) * kStrideA + (l & 7);
 #pragma unroll
         for (int m1 = 0; m1 < 16; ++m1) nv[16 * half + m1] = src[8 * m1];
-        lds_fence();
+        wave_lds_order();
     }
 #pragma unroll
     for (int i = 0; i < 32; ++i) v[i] = nv[i];
@@ -323,12 +334,12 @@ __device__ __forceinline__ void transpose_a_fwd(T (&v)[32], T *xb, int l)
         T *dst = xb + (l >> 3) * kStrideA + (l & 7);
 #pragma unroll
         for (int m1 = 0; m1 < 16; ++m1) dst[8 * m1] = v[16 * half + m1];
-        lds_fence();
+        wave_lds_order();
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk) nv[16 * h + 8 * half + kk] = xb[kk * kStrideA + l + 64 * h];
-        lds_fence();
+        wave_lds_order();
     }
 #pragma unroll
     for (int i = 0; i < 32; ++i) v[i] = nv[i];
@@ -347,13 +358,13 @@ __device__ __forceinline__ void transpose_b_inv(T (&v)[32], T *xb, int l)
 #pragma unroll
             for (int kl = 0; kl < 8; ++kl)
                 xb[xb_b(kl, (l >> 3) + 8 * hp, l & 7)] = v[16 * hp + 8 * hb + kl];
-        lds_fence();
+        wave_lds_order();
 #pragma unroll
         for (int uu = 0; uu < 2; ++uu)
 #pragma unroll
             for (int m2 = 0; m2 < 8; ++m2)
                 nv[8 * (2 * hb + uu) + m2] = xb[xb_b((l >> 4) + 4 * uu, l & 15, m2)];
-        lds_fence();
+        wave_lds_order();
     }
 #pragma unroll
     for (int i = 0; i < 32; ++i) v[i] = nv[i];
@@ -371,13 +382,13 @@ __device__ __forceinline__ void transpose_b_fwd(T (&v)[32], T *xb, int l)
 #pragma unroll
             for (int m2 = 0; m2 < 8; ++m2)
                 xb[xb_b((l >> 4) + 4 * uu, l & 15, m2)] = v[8 * (2 * hb + uu) + m2];
-        lds_fence();
+        wave_lds_order();
 #pragma unroll
         for (int hp = 0; hp < 2; ++hp)
 #pragma unroll
             for (int kl = 0; kl < 8; ++kl)
                 nv[16 * hp + 8 * hb + kl] = xb[xb_b(kl, (l >> 3) + 8 * hp, l & 7)];
-        lds_fence();
+        wave_lds_order();
     }
 #pragma unroll
     for (int i = 0; i < 32; ++i) v[i] = nv[i];
@@ -407,11 +418,11 @@ __device__ __forceinline__ void transpose_a_inv_q(T (&v)[32], T *xb, int l)
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk) xb[kk * kStrideAQ + l] = v[16 * h + 8 * half + kk];
-            lds_fence();
+            wave_lds_order();
             const T *src = xb + (l >> 3) * kStrideAQ + (l & 7);
 #pragma unroll
             for (int m = 0; m < 8; ++m) nv[16 * half + 8 * h + m] = src[8 * m];
-            lds_fence();
+            wave_lds_order();
         }
 #pragma unroll
     for (int i = 0; i < 32; ++i) v[i] = nv[i];
@@ -428,10 +439,10 @@ __device__ __forceinline__ void transpose_a_fwd_q(T (&v)[32], T *xb, int l)
             T *dst = xb + (l >> 3) * kStrideAQ + (l & 7);
 #pragma unroll
             for (int m = 0; m < 8; ++m) dst[8 * m] = v[16 * half + 8 * h + m];
-            lds_fence();
+            wave_lds_order();
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk) nv[16 * h + 8 * half + kk] = xb[kk * kStrideAQ + l];
-            lds_fence();
+            wave_lds_order();
         }
 #pragma unroll
     for (int i = 0; i < 32; ++i) v[i] = nv[i];
@@ -450,10 +461,10 @@ __device__ __forceinline__ void transpose_b_inv_q(T (&v)[32], T *xb, int l)
 #pragma unroll
                 for (int kq = 0; kq < 4; ++kq)
                     xb[xb_b(kq, (l >> 3) + 8 * hp, l & 7)] = v[16 * hp + 8 * hb + 4 * uu + kq];
-            lds_fence();
+            wave_lds_order();
 #pragma unroll
             for (int m2 = 0; m2 < 8; ++m2) nv[8 * (2 * hb + uu) + m2] = xb[xb_b(l >> 4, l & 15, m2)];
-            lds_fence();
+            wave_lds_order();
         }
 #pragma unroll
     for (int i = 0; i < 32; ++i) v[i] = nv[i];
@@ -469,13 +480,13 @@ __device__ __forceinline__ void transpose_b_fwd_q(T (&v)[32], T *xb, int l)
         for (int uu = 0; uu < 2; ++uu) {
 #pragma unroll
             for (int m2 = 0; m2 < 8; ++m2) xb[xb_b(l >> 4, l & 15, m2)] = v[8 * (2 * hb + uu) + m2];
-            lds_fence();
+            wave_lds_order();
 #pragma unroll
             for (int hp = 0; hp < 2; ++hp)
 #pragma unroll
                 for (int kq = 0; kq < 4; ++kq)
                     nv[16 * hp + 8 * hb + 4 * uu + kq] = xb[xb_b(kq, (l >> 3) + 8 * hp, l & 7)];
-            lds_fence();
+            wave_lds_order();
         }
 #pragma unroll
     for (int i = 0; i < 32; ++i) v[i] = nv[i];

@@ -50,6 +50,9 @@ __device__ __forceinline__ GNSS_GLOBAL T *gmem(T *p)
     return (GNSS_GLOBAL T *)p;
 }
 
+typedef float f4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+
 // A workgroup-uniform 64-bit value in scalar registers.
 __device__ __forceinline__ long long uniform64(long long v)
 {
@@ -722,13 +725,16 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(WPE))) v
                         // the block spectrum is re-read for every PRN of the tile (L1/L2
                         // hits after the first) rather than pinned in registers
                         float2 z[32];
-                        const float4 *gq = gp;
-                        asm volatile("" : "+v"(gq));
+                        // (the cast keeps them global loads: the compiler cannot tell
+                        // behind the opaque pointer, and flat loads wait with the LDS)
+                        const float4 *gv = gp;
+                        asm volatile("" : "+v"(gv));
+                        const GNSS_GLOBAL f4v *gq = (const GNSS_GLOBAL f4v *)gv;
                         phase_barrier();
 #pragma unroll
                         for (int jj = 0; jj < 16; ++jj) {
-                            float4 t = gq[jj * 64 + l];
-                            float4 c = s_cc[p * kVec + jj * 64 + l];
+                            const f4v t = gq[jj * 64 + l];
+                            const float4 c = s_cc[p * kVec + jj * 64 + l];
                             z[2 * jj] = c_mul(make_float2(t.x, t.y), make_float2(c.x, c.y));
                             z[2 * jj + 1] = c_mul(make_float2(t.z, t.w), make_float2(c.z, c.w));
                         }
@@ -1057,13 +1063,14 @@ __global__ __launch_bounds__(64 * kCorrWavesH) __attribute__((amdgpu_waves_per_e
                 for (int pp = 0; pp < NP; ++pp) {
                     const __half2 dre = __floats2half2_rn(kdc[2 * pp] * ds.x, kdc[2 * pp + 1] * ds.x);
                     const __half2 dim = __floats2half2_rn(kdc[2 * pp] * ds.y, kdc[2 * pp + 1] * ds.y);
-                    const uint4 *gq = Gh + vec * 512;
-                    asm volatile("" : "+v"(gq));
+                    const uint4 *gv = Gh + vec * 512;
+                    asm volatile("" : "+v"(gv));
+                    const GNSS_GLOBAL u4v *gq = (const GNSS_GLOBAL u4v *)gv;  // global, not flat, loads
                     phase_barrier();
                     hc2 z[32];
 #pragma unroll
                     for (int jj = 0; jj < 8; ++jj) {
-                        const uint4 g = gq[jj * 64 + l];
+                        const u4v g = gq[jj * 64 + l];
                         const uint4 c0 = s_cc[pp * 1024 + (2 * jj) * 64 + l];
                         const uint4 c1 = s_cc[pp * 1024 + (2 * jj + 1) * 64 + l];
                         z[4 * jj + 0] = c_mul_bcast(bits_h2(g.x), make_hc2(bits_h2(c0.x), bits_h2(c0.y)));
