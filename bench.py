@@ -43,7 +43,9 @@ CORR_KERNEL = {"fp32": "k_corr", "fp16": "k_corr_h", "fp16pfa": "k_corr_x"}
 # what bounds each mode's correlation kernel, and that unit's peak
 ROOF = {"fp32": ("alu", 157.3), "fp16": ("alu", 157.3), "fp16pfa": ("mfma", PEAK_MFMA_F16_TFLOPS)}
 # bytes of one stored block spectrum (one polyphase vector)
-G_VEC_BYTES = {"fp32": 16384, "fp16": 8192, "fp16pfa": 4224}
+G_VEC_BYTES = {"fp32": 24576, "fp16": 8192, "fp16pfa": 4224}
+# bytes of one polyphase vector in memory before its transform (FP32 keeps it in LDS)
+F_VEC_BYTES = {"fp32": 0, "fp16": 8192, "fp16pfa": 8192}
 # matrix-core flops of one 1023-point inverse transform in the exact-length
 # mode: 54 16x16x32 FP16 products of 16384 flops each
 PFA_MFMA_FLOPS = 54 * 16384
@@ -101,7 +103,7 @@ def workload(name: str, code_fn):
         snap, srch = synth.weak_complex_int8(code_fn, seed=2, fs=10000000)
         desc = ("weak-signal complex int8 baseband at a general rate, fs 10.000 MHz, 100 ms, 8 planted; "
                 "32 PRN x 121 Doppler (+-7.5 kHz / 125 Hz) x 10000 phases, 4 ms coh x 25 noncoh "
-                "(zero-padded 32768-point FP32 transforms)")
+                "(zero-padded FP32 transforms)")
     elif name == "long":
         snap, srch = synth.long_complex_int8(code_fn, seed=3)
         desc = ("long weak-signal integration, complex int8 baseband, fs 16.368 MHz, 2.048 s, 8 planted at "
@@ -320,16 +322,17 @@ def main():
         # a rate that is not a multiple of the chip rate: the zero-padded FP32
         # transforms in every precision
         roofline = corr_roofline("fp32", units * flops_unit, corr_ms, read_traffic("gen_corr", wl), 0)
-        # N > 4096: the 16384-point (four-step) kernel; else the radix-8 one of its length
-        roofline["kernel"] = "k_gen_corr16" if N > 4096 else "k_gen_corr"
+        # N > 2048 (and many items from N = 1366 on): transforms in rows of 2048 points;
+        # else the radix-8 kernel of its length
+        roofline["kernel"] = "k_gen_corr_rows" if N > 2048 or (N > 1365 and n_prn * nd > 256) else "k_gen_corr"
     else:
         kern = CORR_KERNEL[args.precision]
         roofline = corr_roofline(args.precision, units * flops_unit, corr_ms, read_traffic(kern[2:], wl),
                                  units * (N // 1023))
 
     # the FFT pipeline (forward FFT + correlation stages) against the HBM roofline:
-    # staged-model bytes, each stage buffer crossing HBM once (F in, G out, G in,
-    # grid out; general rates: the folded-block spectra out and in, the grid out),
+    # staged-model bytes, each stage buffer crossing HBM once (F in for the FP16
+    # modes, G out, G in, grid out; general rates: the folded-block spectra out and in, the grid out),
     # over the two stages' measured time
     if general:
         M = 64
@@ -341,7 +344,7 @@ def main():
     else:
         n_vec = nd * srch.N_noncoh * (N // 1023)
         g_vec = G_VEC_BYTES[args.precision]
-        staged = n_vec * (8192 + 2 * g_vec) + n_prn * nd * N * 4
+        staged = n_vec * (F_VEC_BYTES[args.precision] + 2 * g_vec) + n_prn * nd * N * 4
     pipe_ms = (stages["fft"][0] + stages["corr"][0]) / args.steps
     fft_hbm = {"staged_bytes": staged, "time_ms": round(pipe_ms, 4),
                "achieved_GBs": round(staged / (pipe_ms / 1e3) / 1e9, 1), "peak_GBs": PEAK_HBM_GBS,

@@ -82,6 +82,10 @@ __device__ __forceinline__ float2 c_mulc(float2 a, float2 b)  // a * conj(b)
 {
     return make_float2(fmaf(a.x, b.x, a.y * b.y), fmaf(a.y, b.x, -a.x * b.y));
 }
+__device__ __forceinline__ float2 c_mul_add(float2 a, float2 b, float2 z)  // z + a * b
+{
+    return make_float2(fmaf(a.x, b.x, fmaf(-a.y, b.y, z.x)), fmaf(a.x, b.y, fmaf(a.y, b.x, z.y)));
+}
 __device__ __forceinline__ float2 c_mulc_add(float2 a, float2 b, float2 z)  // z + a * conj(b)
 {
     return make_float2(fmaf(a.x, b.x, fmaf(a.y, b.y, z.x)), fmaf(a.y, b.x, fmaf(-a.x, b.y, z.y)));
@@ -224,6 +228,44 @@ __device__ __forceinline__ void dft8(T (&a)[LEN])
         a[OFF + 6] = c_sub(e2, o2);
         a[OFF + 7] = c_sub(e3, o3);
     }
+}
+
+// a * W_8^K * sqrt(2) (K = 1, 3), unscaled
+template <int K, bool INV>
+__device__ __forceinline__ float2 tw8_unscaled(float2 a)
+{
+    if constexpr (K == 1)
+        return INV ? make_float2(a.x - a.y, a.x + a.y) : make_float2(a.x + a.y, a.y - a.x);
+    else
+        return INV ? make_float2(-a.x - a.y, a.x - a.y) : make_float2(a.y - a.x, -a.x - a.y);
+}
+// e + r u
+__device__ __forceinline__ float2 c_fma(float r, float2 u, float2 e)
+{
+    return make_float2(fmaf(r, u.x, e.x), fmaf(r, u.y, e.y));
+}
+
+// The rest of an 8-point DFT after its first stage's sums s[n] = a[n] + a[n +
+// 4] and differences d[n] = a[n] - a[n + 4]; the factor 1/sqrt(2) of W_8 goes
+// into the last additions.
+template <bool INV>
+__device__ __forceinline__ void dft8_rest(const float2 (&s)[4], const float2 (&d)[4], float2 *o)
+{
+    constexpr float r = 0.70710678118654752440f;
+    const float2 e0 = c_add(s[0], s[2]), e2 = c_sub(s[0], s[2]);
+    const float2 t3 = tw<4, 1, INV>(d[2]);
+    const float2 e1 = c_add(d[0], t3), e3 = c_sub(d[0], t3);
+    const float2 p0 = c_add(s[1], s[3]), p2 = tw<4, 1, INV>(c_sub(s[1], s[3]));
+    const float2 u3 = tw<4, 1, INV>(d[3]);
+    const float2 p1 = tw8_unscaled<1, INV>(c_add(d[1], u3)), p3 = tw8_unscaled<3, INV>(c_sub(d[1], u3));
+    o[0] = c_add(e0, p0);
+    o[4] = c_sub(e0, p0);
+    o[1] = c_fma(r, p1, e1);
+    o[5] = c_fma(-r, p1, e1);
+    o[2] = c_add(e2, p2);
+    o[6] = c_sub(e2, p2);
+    o[3] = c_fma(r, p3, e3);
+    o[7] = c_fma(-r, p3, e3);
 }
 
 // 16-point DFT on registers a[OFF .. OFF+16): 4 x 4 four-step.

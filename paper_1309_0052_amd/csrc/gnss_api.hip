@@ -377,7 +377,8 @@ void build_batch(const gnss::Plan *plans, const gnss_request *reqs, int n, gnss:
             p.detect ? (long long)p.n_prn : 0,
             fd_a, fd_b,
             p.gen ? (p.n_prn + (long long)p.n_dopp * p.Nnc) * (p.gen_seg ? 2 : 1) : 0,
-            p.gen ? cdiv(p.n_prn, d.gen_rows ? gnss::gen_group(d.gen_P) : 1) * p.n_dopp : 0};
+            p.gen ? cdiv(p.n_prn, d.gen_rows ? gnss::gen_group(d.gen_P) : 1) * p.n_dopp : 0,
+            p.gen ? 0 : (long long)p.n_dopp * p.Nnc * gnss::bf_parts(p.spc)};
         for (int st = 0; st < gnss::kNumStages; ++st) {
             B.pre[(size_t)st * (n + 1) + r] = tot[st];
             tot[st] += cnt[st];
@@ -394,8 +395,11 @@ void build_batch(const gnss::Plan *plans, const gnss_request *reqs, int n, gnss:
     B.corr_pt = corr_pt;
     B.corr_w = corr_w;
     B.precision = precision;
-    // the frequency-domain variant has no polyphase vectors in F: its long spectra live there
-    B.F_bytes = doppler_fd ? (size_t)fd_f2 * sizeof(float2) : (size_t)vec * gnss::kPolyLen * sizeof(int2);
+    // the frequency-domain variant has no polyphase vectors in F: its long spectra live
+    // there; FP32 searches keep them in LDS
+    B.F_bytes = doppler_fd ? (size_t)fd_f2 * sizeof(float2)
+                : precision == GNSS_FP32 ? 0
+                                         : (size_t)vec * gnss::kPolyLen * sizeof(int2);
     // the general-rate block and code spectra (FP32 complex) follow the polyphase spectra
     B.gen_off = align256(gnss::g_bytes(vec, precision));
     B.G_bytes = B.gen_off + (size_t)gen_f2 * sizeof(float2);
@@ -692,7 +696,10 @@ int ctx_init_tables(gnss_ctx *c)
     HIP_TRY(gnss::launch_lut(c->d_lut, nullptr, nullptr, c->stream));
     HIP_TRY(gnss::launch_gold_codes(c->d_codes, c->stream));
     HIP_TRY(gnss::launch_twiddles(c->d_tw, c->stream));
-    HIP_TRY(gnss::launch_code_spectra(c->d_codes, c->d_tw, c->d_cs, c->stream));
+    if (c->precision == GNSS_FP32)
+        HIP_TRY(gnss::launch_code_spectra3(c->d_codes, (float2 *)c->d_cs, c->stream));
+    else
+        HIP_TRY(gnss::launch_code_spectra(c->d_codes, c->d_tw, c->d_cs, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     if (h) {
         // common exponent of the FP16 code spectra: max |C| * 2^-cs_exp <= 1

@@ -103,6 +103,8 @@ hipError_t launch_lut(uint32_t *d_lut_packed, int16_t *d_cos, int16_t *d_sin, hi
 hipError_t launch_twiddles(float2 *d_tw, hipStream_t s);
 hipError_t launch_code_spectra(const uint8_t *d_codes, const float2 *d_tw, float4 *d_cs,
                                hipStream_t s);
+// the FP32 contexts' (1536-point, the same size)
+hipError_t launch_code_spectra3(const uint8_t *d_codes, float2 *d_cs, hipStream_t s);
 // FP16 tables: packed twiddles and the code spectra scaled by 2^-cs_exp
 hipError_t launch_tables_h(const float4 *d_cs, const uint8_t *d_codes, void *d_tw_h, void *d_cs_h, int cs_exp,
                            hipStream_t s);
@@ -121,6 +123,8 @@ hipError_t launch_tables_x_frags(void *d_frags, hipStream_t s);
 hipError_t launch_code_spectra_x(const uint8_t *d_codes, double2 *d_stage, hipStream_t s);
 hipError_t launch_code_spectra_x_pack(const double2 *d_stage, void *d_cs_x, int cs_exp, hipStream_t s);
 
+// FP32: two 1536-point segment spectra per polyphase vector
+constexpr size_t kVecBytes3 = 2 * 1536 * 8;
 // Bytes of the block spectra of n_vec polyphase vectors: FP32 float4
 // storage order; FP16 packed half2 (re, im), followed by one int exponent per
 // vector.
@@ -128,7 +132,7 @@ inline size_t g_spectra_bytes(long long n_vec, int precision)
 {
     return precision == GNSS_FP16 ? (size_t)n_vec * 8192
            : precision == GNSS_FP16_PFA ? (size_t)n_vec * kPfaVecBytes
-                                        : (size_t)n_vec * kVec * 16;
+                                        : (size_t)n_vec * kVecBytes3;
 }
 inline size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 // FP16 modes: the spectra, the per-vector exponents (int) and, for GNSS_FP16,
@@ -146,9 +150,13 @@ inline size_t g_bytes(long long n_vec, int precision)
 // requests (a single request is a batch of one); the correlation kernel can
 // run persistent, the others run one workgroup per work item
 // ---------------------------------------------------------------------------
-// kStGenX / kStGenCorr: the general-rate path (code and block spectra,
-// correlation)
-enum Stage { kStBox = 0, kStVec, kStCorr, kStColmax, kStPeak, kStFdA, kStFdB, kStGenX, kStGenCorr, kNumStages };
+// kStBox: the FP16 modes' wipe and fold, and the stage entry point's; kStBoxFft:
+// the FP32 search's, with its forward transforms; kStGenX / kStGenCorr: the
+// general-rate path (code and block spectra, correlation)
+enum Stage { kStBox = 0, kStVec, kStCorr, kStColmax, kStPeak, kStFdA, kStFdB, kStGenX, kStGenCorr, kStBoxFft,
+             kNumStages };
+// work items of kStBoxFft per (Doppler, block)
+inline __host__ __device__ int bf_parts(int spc) { return spc > 8 ? 2 : 1; }
 constexpr int kXcds = 8;
 
 // One request as the kernels see it (device memory).

@@ -13,30 +13,34 @@
 //   R[spc q + s] = sum_m g_s[m] C[(m - q) mod 1023],
 //   g_s[m] = F[spc m + s],  F[n] = sum_{t<spc} f[(n + t) mod N]
 // (a boxcar over one chip, then a polyphase split).  Each g_s is correlated
-// with the chip-rate code through 2048-point transforms (zero padding makes
-// the circular length-1023 correlation a linear one), so one code spectrum
-// per PRN serves every sample rate, and each transform lives in one
-// wavefront's registers.
+// with the chip-rate code through zero-padded transforms (padding makes the
+// circular length-1023 correlation a linear one), so one code spectrum per PRN
+// serves every sample rate, and each transform lives in one wavefront's
+// registers.  FP32 contexts take g_s in two segments on 1536-point transforms
+// (fft1536.hpp), FP16 ones 2048-point transforms (fft2048.hpp).
 //
 // Kernel sequence of a batch (every kernel walks a device table of the batch's
 // requests; a single request is a batch of one):
 //   k_reset          clears the work counters (a kernel, so the sequence can be
 //                    captured in a graph)
-//   k_box            NCO wipe-off + coherent fold + boxcar + polyphase split
-//                    (exact int32)                     -> F[k][b][s][1024]
-//   k_fft_poly       forward 2048-point FFT of every g_s -> G (storage order)
+//   k_box_fft        NCO wipe-off + coherent fold + boxcar + polyphase split
+//                    (exact int32) + forward FFT of every g_s -> G (storage order)
 //   k_corr           per (PRN tile, Doppler, phase): G * conj(code spectrum),
 //                    IFFT, |.|^2, sum over blocks in registers -> grid
 //   k_colmax/k_peak  column max over Doppler, argmax, second peak, mean
 //   k_interp         FP64 parabolic refinement
-// FP16 contexts use k_fft_poly_h and k_corr_h (packed half precision with
-// per-vector power-of-two scaling).  k_track computes the tracking channel's
+// FP16 contexts use k_box (the polyphase values to memory, F[k][b][s][1024]),
+// k_fft_poly_h and k_corr_h (packed half precision with per-vector
+// power-of-two scaling).  k_track computes the tracking channel's
 // early / prompt / late correlators (Fig. 3).
+#include "fft1536.hpp"
 #include "fft2048.hpp"
 #include "gnss_internal.hpp"
 #include "pfa1023.hpp"
 
 #include <math.h>
+
+#include <algorithm>
 
 namespace gnss {
 
@@ -52,6 +56,16 @@ __device__ __forceinline__ GNSS_GLOBAL T *gmem(T *p)
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+
+// f(std::integral_constant<int, i>()) for i < N, in order
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void unrolled(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        unrolled<N, I + 1>(f);
+    }
+}
 
 // A workgroup-uniform 64-bit value in scalar registers.
 __device__ __forceinline__ long long uniform64(long long v)
@@ -227,6 +241,41 @@ __global__ __launch_bounds__(256) void k_code_spectra(const uint8_t *codes, cons
         dst[jj * 64 + l] = make_float4(v[2 * jj].x, -v[2 * jj].y, v[2 * jj + 1].x, -v[2 * jj + 1].y);
 }
 
+// FP32 contexts: conj(DFT_1536(cc_i)) of the two segments' replicas (see
+// fft1536.hpp), the c < 2 thirds, [prn][segment][c][kappa], in FP64 and rounded
+// once; row 0 is all zeros.  One thread per value.
+__global__ __launch_bounds__(256) void k_code_spectra3(const uint8_t *codes, float2 *cs)
+{
+    __shared__ double2 s_w[kLen3];
+    __shared__ int8_t s_c[kCodeLen];
+    const int prn = blockIdx.y, idx = blockIdx.x * 256 + threadIdx.x;
+    for (int i = threadIdx.x; i < kLen3; i += 256) {
+        double sn, cn;
+        sincospi((double)i / (kLen3 / 2), &sn, &cn);
+        s_w[i] = make_double2(cn, sn);
+    }
+    for (int i = threadIdx.x; i < kCodeLen; i += 256) s_c[i] = prn ? (int8_t)(1 - 2 * (int)codes[prn * kCodeLen + i]) : 0;
+    __syncthreads();
+    const int seg = idx >> 10, c = (idx >> 9) & 1, k = (3 * (idx & 511) + 512 * c) % kLen3;
+    double re = 0.0, im = 0.0;
+    // u in [-1022, 511]: cc[u] = C[(512 seg + u) mod 1023], times e^(2 pi i k u / 1536)
+    int j = (kSeg3 * seg + 1) % kCodeLen, e = (int)((long long)k * (kLen3 - (kCodeLen - 1)) % kLen3);
+    for (int u = -(kCodeLen - 1); u < kSeg3; ++u) {
+        re += s_c[j] * s_w[e].x;
+        im += s_c[j] * s_w[e].y;
+        if (++j == kCodeLen) j = 0;
+        e += k;
+        if (e >= kLen3) e -= kLen3;
+    }
+    cs[(long long)prn * kCode3 + idx] = make_float2((float)re, (float)im);
+}
+
+hipError_t launch_code_spectra3(const uint8_t *d_codes, float2 *d_cs, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_code_spectra3, dim3(kCode3 / 256, kMaxPrn + 1), dim3(256), 0, s, d_codes, d_cs);
+    return hipGetLastError();
+}
+
 hipError_t launch_code_spectra(const uint8_t *d_codes, const float2 *d_tw, float4 *d_cs,
                                hipStream_t s)
 {
@@ -370,17 +419,53 @@ __device__ __forceinline__ long long next_item(BatchHdr *h, int stage, long long
 // one (request, Doppler, block), done in chunks of kBoxChunk outputs, each
 // wiping the spc - 1 samples past it as a halo.  All integer, exact.
 // ===========================================================================
+// Mixing by integer dot products.  A sample as two 16-bit halves (re, im) and
+// a table entry {(cos, sin), (-sin, cos)} give y = x (cos - j sin), added to
+// (yr, yi), in two v_dot2_i32_i16: exact (|x| <= 127, |LUT| <= 4096, 32-bit
+// sums), 7 vector instructions per sample with decode and phase where
+// separate bytes and products took about 20.
+typedef short s2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void mix_add(s2v x, uint2 e, int &yr, int &yi)
+{
+    yr = __builtin_amdgcn_sdot2(x, __builtin_bit_cast(s2v, e.x), yr, false);
+    yi = __builtin_amdgcn_sdot2(x, __builtin_bit_cast(s2v, e.y), yi, false);
+}
+// The table in LDS from the packed (cos, sin) one.
+__device__ __forceinline__ void stage_mix_lut(uint2 *s_lut, const uint32_t *lut, int tid, int nthreads)
+{
+    for (int i = tid; i < 1024; i += nthreads) {
+        const uint32_t v = lut[i];
+        s_lut[i] = make_uint2(v, ((0u - (v >> 16)) & 0xFFFFu) | (v << 16));
+    }
+}
+// Sample `off` (bytes; sample index if packed) of a record segment at p.
+template <int FMT>
+__device__ __forceinline__ s2v load_mix(const GNSS_GLOBAL uint8_t *p, uint32_t off)
+{
+    if constexpr (FMT == GNSS_CPLX_I8) {
+        const uint32_t v = *(const GNSS_GLOBAL uint16_t *)(p + off);  // I in the low byte
+        // (256 I, 256 Q), then the sign-extending shifts
+        return __builtin_bit_cast(s2v, __builtin_amdgcn_perm(v, v, 0x010C000Cu)) >> 8;
+    } else if constexpr (FMT == GNSS_REAL_I8) {
+        return s2v{(short)(int8_t)p[off], 0};
+    } else {
+        const uint32_t code = (p[off >> 2] >> (2u * (off & 3u))) & 3u;
+        // 00:+1 01:+3 10:-1 11:-3
+        const int mag = (code & 1u) ? 3 : 1;
+        return s2v{(short)((code & 2u) ? -mag : mag), 0};
+    }
+}
+
 constexpr int kBoxRun = 8;
 __device__ __forceinline__ int bpad(int i) { return i + (i >> 3); }  // bank-conflict padding
 
 // Wipe + fold of samples n0 .. n0 + len - 1 (mod N) of block b into s_f,
 // FMT-specialised; the phase of the folded milliseconds advances by N D (mod
-// 2^32) from one to the next, and |x| <= 127, |LUT| <= 4096 make the 24-bit
-// multiplies exact.  Same values as wipe_fold_one.  Samples are addressed from
+// 2^32) from one to the next.  Same values as wipe_fold_one.  Samples are addressed from
 // the block's first byte (the same pointer in every thread) by 32-bit in-block
 // offsets: a block holds Tc N <= 64 * 16368 samples.
 template <int FMT, int NT>
-__device__ __forceinline__ void box_wipe(const void *samples, int N, int Tc, const uint32_t *s_lut, uint32_t D,
+__device__ __forceinline__ void box_wipe(const void *samples, int N, int Tc, const uint2 *s_lut, uint32_t D,
                                          int b, int n0, int len, int shift, int2 *s_f)
 {
     const uint32_t dN = (uint32_t)N * D;
@@ -402,30 +487,7 @@ __device__ __forceinline__ void box_wipe(const void *samples, int N, int Tc, con
         int yr = 0, yi = 0;
 #pragma unroll 4
         for (int c = 0; c < Tc; ++c) {
-            int xr, xi;
-            if (FMT == GNSS_CPLX_I8) {
-                const uint32_t v = *(const GNSS_GLOBAL uint16_t *)(blk + off);  // I in the low byte
-                xr = (int)(int8_t)(v & 0xFFu);
-                xi = (int)(int8_t)(v >> 8);
-            } else if (FMT == GNSS_REAL_I8) {
-                xr = (int)(int8_t)blk[off];
-                xi = 0;
-            } else {
-                const uint32_t code = (blk[off >> 2] >> (2u * (off & 3u))) & 3u;
-                // 00:+1 01:+3 10:-1 11:-3
-                const int mag = (code & 1u) ? 3 : 1;
-                xr = (code & 2u) ? -mag : mag;
-                xi = 0;
-            }
-            const uint32_t e = s_lut[ph >> 22];
-            const int cs = (int)(int16_t)(e & 0xFFFFu), sn = (int)(int16_t)(e >> 16);
-            if (FMT == GNSS_CPLX_I8) {
-                yr += __mul24(xr, cs) + __mul24(xi, sn);
-                yi += __mul24(xi, cs) - __mul24(xr, sn);
-            } else {
-                yr += __mul24(xr, cs);
-                yi -= __mul24(xr, sn);
-            }
+            mix_add(load_mix<FMT>(blk, off), s_lut[ph >> 22], yr, yi);
             off += step;
             ph += dN;
         }
@@ -440,7 +502,7 @@ constexpr int kBoxBuf = (kBoxChunk + kMaxSpc) + (kBoxChunk + kMaxSpc) / 8 + 8;
 // of request d by NT threads: dst[s * kPolyLen + m] = F[spc m + s] for m <
 // 1023 and 0 at m = 1023 (dst: the item's polyphase vectors in F).
 template <int NT, typename DstPtr>
-__device__ __forceinline__ void box_item(const ReqDesc &d, int k, int b, const uint32_t *s_lut, int2 *s_f,
+__device__ __forceinline__ void box_item(const ReqDesc &d, int k, int b, const uint2 *s_lut, int2 *s_f,
                                          DstPtr dst)
 {
     const int N = d.N, spc = d.spc;
@@ -494,9 +556,9 @@ __global__ __launch_bounds__(256) void k_box(const ReqDesc *__restrict__ R, Batc
                                              const uint32_t *lut, int2 *F)
 {
     __shared__ int2 s_f[kBoxBuf];
-    __shared__ uint32_t s_lut[1024];
+    __shared__ uint2 s_lut[1024];
     __shared__ long long s_item;
-    for (int i = threadIdx.x; i < 1024; i += 256) s_lut[i] = lut[i];
+    stage_mix_lut(s_lut, lut, threadIdx.x, 256);
     const int n_req = H->n_req;
     const long long total = H->total[kStBox];
     const long long *pst = pre + (long long)kStBox * (n_req + 1);
@@ -515,37 +577,183 @@ __global__ __launch_bounds__(256) void k_box(const ReqDesc *__restrict__ R, Batc
 }
 
 // ===========================================================================
-// stage A2: forward 2048-point FFT of every polyphase component (one wave
-// per vector; vectors of all requests are contiguous in F and G)
+// stage A, FP32: wipe, fold, boxcar, polyphase split and forward transforms in
+// one kernel.  A work item is 8192 outputs F[n] at most: one segment (512
+// values of m) of a (Doppler, block) with more than 8 samples per chip, else
+// both.  The 512 threads wipe and fold the item's samples into LDS, sum the
+// boxcars in runs of 16 outputs held in registers, write them back split by
+// (segment, phase) and each wave transforms the segments w and w + 8.  What
+// bounds it is the write of the spectra (24 KB per (Doppler, block, phase));
+// the polyphase values, written and read again by two kernels before, stay in
+// LDS.  78 KB of LDS: two workgroups per CU, so that one's transforms overlap
+// the other's sample loads.  Measured on the
+// weak-signal search (121 bins x 25 blocks x 16 phases, 1.19 GB of spectra):
+// 0.32 ms, 3.7 TB/s, against 0.17 + 0.27 ms for the two kernels it replaces.
 // ===========================================================================
-__global__ __launch_bounds__(256) void k_fft_poly(const int2 *F, const float2 *tw, float4 *G,
-                                                  const BatchHdr *H)
+constexpr int kBfThreads = 512, kBfOut = 8192, kBfRun = 16, kBfSlots = 16;
+static_assert(kBfThreads * kBfRun == kBfOut, "one run per thread");
+__device__ __forceinline__ int bf_pad(int i) { return i + (i >> 4); }  // runs of 16 at stride 17: no bank conflicts
+static_assert((kBfOut + 2 * kMaxSpc) * 17 / 16 + 1 <= kBfSlots * kXbuf3, "samples and transforms share the LDS");
+
+// Wipe + fold of samples n0 + i, i = i0 + tid + 512 j < len (j < 9), of block b
+// into s_f, the arithmetic of box_wipe with the nine samples' loads of a
+// millisecond in flight together.
+template <int FMT>
+__device__ __forceinline__ void bf_wipe(const ReqDesc &d, const uint2 *s_lut, uint32_t D, int b, int n0, int i0,
+                                        int len, int2 *s_f)
 {
-    __shared__ float2 s_tw[kTwElems];
-    __shared__ float2 s_xb[4][kXbufElemsQ];  // transposes in quarters: fewer LDS bank conflicts
-    stage_twiddles(s_tw, tw, threadIdx.x, 256);
-    __syncthreads();
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const long long n_vec = H->total[kStVec];
-    for (long long vec = (long long)blockIdx.x * 4 + w; vec < n_vec; vec += (long long)gridDim.x * 4) {
-        const int2 *src = F + vec * kPolyLen;
-        float2 v[32];
+    constexpr int J = 9;
+    const int N = d.N, Tc = d.Tc;
+    const uint32_t dN = (uint32_t)N * D;
+    const long long base = (long long)b * Tc * N;
+    // 2-bit packed records: the block may start inside a byte
+    const uint32_t sub = FMT == GNSS_REAL_2BIT_PACKED ? (uint32_t)(base & 3) : 0u;
+    const long long blk_byte = FMT == GNSS_CPLX_I8 ? 2 * base : FMT == GNSS_REAL_I8 ? base : (base >> 2);
+    const GNSS_GLOBAL uint8_t *blk = (const GNSS_GLOBAL uint8_t *)d.samples + blk_byte;
+    const uint32_t step = FMT == GNSS_CPLX_I8 ? 2u * (uint32_t)N : (uint32_t)N;  // bytes (samples if packed)
+    uint32_t off[J], ph[J];
+    int yr[J], yi[J];
+    const uint32_t ph0 = (uint32_t)(base + n0 + i0 + (int)threadIdx.x) * D;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+    for (int j = 0; j < J; ++j) {
+        const int i = i0 + (int)threadIdx.x + kBfThreads * j;
+        int n = n0 + i;  // in (-N, 2N): the block read circularly, N D (mod 2^32) of phase back or on
+        uint32_t p = ph0 + (uint32_t)(kBfThreads * j) * D;
+        if (n < 0) {
+            n += N;
+            p += dN;
+        }
+        if (n >= N) {
+            n -= N;
+            p -= dN;
+        }
+        if (i >= len) n = 0;  // not stored
+        ph[j] = p;
+        off[j] = FMT == GNSS_CPLX_I8 ? 2u * (uint32_t)n : (uint32_t)n + sub;
+        yr[j] = 0;
+        yi[j] = 0;
+    }
+#pragma unroll 1
+    for (int c = 0; c < Tc; ++c) {
 #pragma unroll
-            for (int k2b = 0; k2b < 8; ++k2b) {
-                if (k2b < 4) {
-                    int2 t = src[l + 64 * u + 256 * k2b];
-                    v[8 * u + k2b] = make_float2((float)t.x, (float)t.y);
-                } else {
-                    v[8 * u + k2b] = make_float2(0.f, 0.f);
+        for (int j = 0; j < J; ++j) {
+            mix_add(load_mix<FMT>(blk, off[j]), s_lut[ph[j] >> 22], yr[j], yi[j]);
+            if (FMT == GNSS_REAL_2BIT_PACKED) off[j] += step;
+            ph[j] += dN;
+        }
+        if (FMT != GNSS_REAL_2BIT_PACKED) blk += step;
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int i = i0 + (int)threadIdx.x + kBfThreads * j;
+        if (i < len) s_f[bf_pad(i)] = make_int2(yr[j], yi[j]);
+    }
+}
+
+__global__ __launch_bounds__(kBfThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_box_fft(
+    const ReqDesc *__restrict__ R, const BatchHdr *H, const long long *pre, const uint32_t *lut, const float2 *twg,
+    float4 *G)
+{
+    __shared__ float2 s_x[kBfSlots * kXbuf3];
+    __shared__ uint2 s_lut[1024];
+    int2 *s_f = (int2 *)s_x;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    stage_mix_lut(s_lut, lut, tid, kBfThreads);
+    const int n_req = H->n_req;
+    const long long total = H->total[kStBoxFft];
+    const long long *pst = pre + (long long)kStBoxFft * (n_req + 1);
+    const long long id = xcd_remap(blockIdx.x, gridDim.x);
+    for (long long it = id; it < total; it += gridDim.x) {
+        const int r = find_req(pst, n_req, it);
+        const ReqDesc &d = R[r];
+        const int N = d.N, spc = d.spc;
+        const int parts = bf_parts(spc);
+        const int local = (int)(it - pst[r]);
+        const int kb = local / parts, part = local - kb * parts;
+        const int k = kb / d.Nnc, b = kb - k * d.Nnc;
+        const uint32_t D = d.dk[k];
+        // code-Doppler drift of this (bin, block) in samples, in [0, N): delaying
+        // the folded block by it circularly shifts its correlation by as many lags
+        const int shift = d.cshift ? d.cshift[kb] : 0;
+        const int n0 = part * kSeg3 * spc;  // first output
+        const int cnt = min(N - n0, parts == 2 ? kSeg3 * spc : N), len = cnt + spc - 1;
+        __syncthreads();  // the table is staged; the previous item's transforms are done
+        for (int i0 = 0; i0 < len; i0 += 9 * kBfThreads) {
+            if (d.fmt == GNSS_CPLX_I8)
+                bf_wipe<GNSS_CPLX_I8>(d, s_lut, D, d.b0 + b, n0 - shift, i0, len, s_f);
+            else if (d.fmt == GNSS_REAL_I8)
+                bf_wipe<GNSS_REAL_I8>(d, s_lut, D, d.b0 + b, n0 - shift, i0, len, s_f);
+            else
+                bf_wipe<GNSS_REAL_2BIT_PACKED>(d, s_lut, D, d.b0 + b, n0 - shift, i0, len, s_f);
+        }
+        __syncthreads();
+        float2 o[kBfRun];
+        const int i0 = tid * kBfRun;
+        if (i0 < cnt) {
+            int sx = 0, sy = 0;
+            const int2 *run = s_f + bf_pad(i0);  // i0 + t at run[bf_pad(t)]; samples past len are not used
+            for (int t = 0; t < spc; ++t) {
+                const int2 v = run[t];
+                sx += v.x;
+                sy += v.y;
+            }
+#pragma unroll
+            for (int j = 0; j < kBfRun; ++j) {
+                o[j] = make_float2((float)sx, (float)sy);
+                if (j + 1 < kBfRun) {
+                    const int2 vi = run[bf_pad(j + spc)], vo = run[j];
+                    sx += vi.x - vo.x;
+                    sy += vi.y - vo.y;
+                }
+                if (j % 4 == 3) phase_barrier();
+            }
+        }
+        __syncthreads();  // the samples are read
+        // slot s of a part, or slot (segment, s) of a whole block: F[spc m + s] at m mod 512
+        if (i0 < cnt) {
+            const int n = n0 + i0;
+            int m = n / spc, s = n - m * spc;
+#pragma unroll
+            for (int j = 0; j < kBfRun; ++j) {
+                if (i0 + j < cnt) {
+                    const int slot = parts == 2 ? s : (m >> 9) * spc + s;
+                    s_x[slot * kXbuf3 + (m & (kSeg3 - 1))] = o[j];
+                }
+                if (++s == spc) {
+                    s = 0;
+                    ++m;
                 }
             }
-        fft2048<true, true>(v, s_xb[w], s_tw, s_tw + kT1Elems, l);
-        float4 *dst = G + vec * kVec;
+        }
+        // the second segment's value 511 (m = 1023) is zero
+        if (tid < spc && (parts == 1 || part == 1))
+            s_x[(parts == 2 ? tid : spc + tid) * kXbuf3 + kSeg3 - 1] = make_float2(0.f, 0.f);
+        int l = tid & 63;
+        asm volatile("" : "+v"(l));  // the twiddle addresses are formed here, not hoisted and held
+        const Lane3 lw(twg, l);
+        __syncthreads();
+        const int slots = parts == 2 ? spc : 2 * spc;
+        {
+            for (int slot = w; slot < slots; slot += kBfThreads / 64) {
+                const int sg = parts == 2 ? part : slot / spc, s = parts == 2 ? slot : slot - sg * spc;
+                float2 *xb = s_x + slot * kXbuf3;  // the slot's own LDS carries its exchanges
+                float2 x[8];
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj)
-            dst[jj * 64 + l] = make_float4(v[2 * jj].x, v[2 * jj].y, v[2 * jj + 1].x, v[2 * jj + 1].y);
+                for (int j = 0; j < 8; ++j) x[j] = xb[l + 64 * j];
+                wave_lds_order();
+                float4 *dst = G + (d.vec_off + (long long)kb * spc + s) * kVec3 + sg * kSpec3;
+                auto third = [&](auto cc) {
+                    constexpr int c = decltype(cc)::value;
+                    float2 v[8];
+                    fft1536_seg<c>(x, v, xb, lw, l);
+#pragma unroll
+                    for (int p = 0; p < 4; ++p)
+                        dst[(4 * c + p) * 64 + l] = make_float4(v[2 * p].x, v[2 * p].y, v[2 * p + 1].x, v[2 * p + 1].y);
+                    phase_barrier();
+                };
+                unrolled<3>(third);
+            }
+        }
     }
 }
 
@@ -587,7 +795,9 @@ __device__ __forceinline__ void write_rows(const float *st, const ReqDesc &d, in
 // unnormalised 2048-point IFFT and 2^-24 for the LUT scale, times the FP16
 // path's code-spectrum scaling); add: adds them to the grid's sums instead
 // (every wave of the workgroup passes the same flag).
-template <int PT, int W>
+// Sum 4 u + k2b of lane l is lag q = l + 64 (4 u + k2b) with QL (1536-point
+// transforms), else q = l + 64 u + 256 k2b (2048-point ones).
+template <int PT, int W, bool QL>
 __device__ __forceinline__ void store_tile(const float (&acc)[PT][16], float *s_stage, const ReqDesc &d,
                                            int ptile, int chunk, int w, int l, int tid, float scale,
                                            bool add = false)
@@ -600,7 +810,7 @@ __device__ __forceinline__ void store_tile(const float (&acc)[PT][16], float *s_
         for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int k2b = 0; k2b < 4; ++k2b) {
-                int q = l + 64 * u + 256 * k2b;
+                int q = QL ? l + 64 * (4 * u + k2b) : l + 64 * u + 256 * k2b;
                 s_stage[(p * 1024 + q) * kPad + w] = acc[p][4 * u + k2b] * scale;
             }
     __syncthreads();
@@ -615,7 +825,7 @@ __device__ __forceinline__ void store_tile(const float (&acc)[PT][16], float *s_
 // blocks just done to the grid (add) or stores them there (the first group),
 // then clears them; each lane reads back only its own stores, and the final
 // write (store_tile with add, another thread per element) comes after its
-// workgroup barriers.  Lane l holds the lags q = l + 64 u + 256 k2b of the
+// workgroup barriers.  Lane l holds the lags q = l + 64 j of the
 // item (bin k, phase s): grid column s + spc q.
 template <int PT>
 __device__ __forceinline__ void add_group(float (&acc)[PT][16], const ReqDesc &d, int ptile, int k, int s, int l,
@@ -627,54 +837,54 @@ __device__ __forceinline__ void add_group(float (&acc)[PT][16], const ReqDesc &d
         if (pi < d.n_prn) {
             GNSS_GLOBAL float *row = gmem(d.grid) + ((long long)pi * d.n_dopp + k) * d.N + s;
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int k2b = 0; k2b < 4; ++k2b) {
-                    const int q = l + 64 * u + 256 * k2b;
-                    if (q < kCodeLen) {
-                        GNSS_GLOBAL float *o = row + (long long)d.spc * q;
-                        const float v = acc[p][4 * u + k2b] * scale;
-                        *o = add ? *o + v : v;
-                    }
+            for (int j = 0; j < 16; ++j) {
+                const int q = l + 64 * j;
+                if (q < kCodeLen) {
+                    GNSS_GLOBAL float *o = row + (long long)d.spc * q;
+                    const float v = acc[p][j] * scale;
+                    *o = add ? *o + v : v;
                 }
+            }
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[p][i] = 0.f;
     }
 }
 
-// Work item = (request, PRN tile, chunk of kCorrWaves (Doppler, phase)
-// items); one wave per (Doppler, phase) item, looping over the blocks and the
-// tile's PT PRNs with the sums in registers.
-// W waves per workgroup, WPE the waves per SIMD the registers are budgeted for
-// (PRN tile 1 at three waves per SIMD: 164 VGPRs; tiles 2 and 4 at two;
-// tile 4, at the 256-register limit, keeps 12 bytes of its set-up in
-// scratch, stored once per item and reloaded for the final write).
+// Work item = (request, PRN tile, chunk of W (Doppler, phase) items); one wave
+// per (Doppler, phase) item, looping over the blocks and the tile's PT PRNs
+// with the sums in registers.  W waves per workgroup, WPE the waves per SIMD
+// the registers are budgeted for (PRN tile 1 at three waves per SIMD: 165
+// VGPRs; tiles 2 and 4 at two).
+// Bound: vector issue (943 vector instructions per transform, one per 1.8 ns and
+// SIMD; LDS carries 74 KB per transform, three quarters of its rate).  On the
+// weak-signal search (32 PRNs x 121 bins x 25 blocks x 16 phases, 1.55 million
+// transforms) 2.55-2.75 ms, against 3.15-3.3 for one 2048-point transform per
+// block (1 257 instructions, 97 KB); before the twiddles went into registers
+// 2.9, before the thirds' spectra were loaded ahead 3.1.
 template <int PT, int W, int WPE>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(WPE))) void k_corr(const ReqDesc *__restrict__ R, BatchHdr *H,
                                                           const long long *pre, const float4 *G,
-                                                          const float4 *__restrict__ CS,
-                                                          const float2 *__restrict__ tw)
+                                                          const float2 *__restrict__ CS,
+                                                          const float2 *__restrict__ twg)
 {
-    constexpr int kCcBytes = PT * kVec * (int)sizeof(float4);
-    constexpr int kTwBytes = kTwElems * (int)sizeof(float2);
-    // the transposes go through a quarter-size buffer per wave in four rounds:
-    // measured faster than the full buffer (its paired accesses conflict in LDS)
-    constexpr int kXbBytes = W * kXbufElemsQ * (int)sizeof(float2);
+    constexpr int kCcBytes = PT * kCodeLds3 * (int)sizeof(float2);
+    constexpr int kXbBytes = W * kXbuf3 * (int)sizeof(float2);
     constexpr int kStageBytes = PT * 1024 * (W + 1) * (int)sizeof(float);
-    constexpr int kSmem = (kCcBytes + kTwBytes + kXbBytes) > kStageBytes ? (kCcBytes + kTwBytes + kXbBytes)
-                                                                          : kStageBytes;
+    constexpr int kSmem = kCcBytes + kXbBytes > kStageBytes ? kCcBytes + kXbBytes : kStageBytes;
+    // 2^-24 (LUT scale) over the square of the unnormalised transform's length
+    constexpr float kScale = (float)(0x1p-24 / ((double)kLen3 * kLen3));
     __shared__ __align__(16) unsigned char smem[kSmem];
     __shared__ long long s_item;
-    float4 *s_cc = (float4 *)smem;
-    float2 *s_tw = (float2 *)(smem + kCcBytes);
-    float2 *s_xb = (float2 *)(smem + kCcBytes + kTwBytes);
+    float2 *s_cc = (float2 *)smem;
+    float2 *s_xb = (float2 *)(smem + kCcBytes);
     float *s_stage = (float *)smem;  // reused after the transforms
 
     const int tid = threadIdx.x;
     // the wave index as a wave-uniform (scalar) value: the item's bin and
     // phase derived from it stay out of the vector registers
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const Lane3 lw(twg, l);
     const int n_req = H->n_req;
     const long long total = H->total[kStCorr];
     const long long *pst = pre + (long long)kStCorr * (n_req + 1);
@@ -691,16 +901,18 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(WPE))) v
         const int spc = d.spc;
         const int k = item / spc, s = item - k * spc;
 
-        // code spectra of the tile's PRNs and the twiddles (in a persistent
-        // launch this overwrites the staging area of the previous item's
-        // write: the barrier inside next_item separates them)
-        for (int i = tid; i < PT * kVec; i += 64 * W) {
-            int p = i / kVec, e = i - p * kVec;
-            int pi = ptile * PT + p;
-            int prn = pi < d.n_prn ? d.prns[pi] : 0;
-            s_cc[i] = CS[(long long)prn * kVec + e];
+        // code spectra of the tile's PRNs (in a persistent launch this overwrites
+        // the staging area of the previous item's write: the barrier inside
+        // next_item separates them)
+        for (int i = tid; i < PT * kCode3; i += 64 * W) {
+            const int p = i / kCode3, e = i - p * kCode3, sg = e >> 10, m = e & 1023;
+            const int pi = ptile * PT + p;
+            const int prn = pi < d.n_prn ? d.prns[pi] : 0;
+            const float2 v = CS[(long long)prn * kCode3 + e];
+            float2 *dst = s_cc + p * kCodeLds3 + sg * (2 * kSeg3 + 1);
+            dst[m] = v;
+            if (m == kSeg3) dst[2 * kSeg3] = v;
         }
-        stage_twiddles(s_tw, tw, tid, 64 * W);
         __syncthreads();
 
         float acc[PT][16];
@@ -710,50 +922,88 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(WPE))) v
             for (int i = 0; i < 16; ++i) acc[p][i] = 0.f;
 
         if (active) {
-            float2 *xb = s_xb + w * kXbufElemsQ;
+            float2 *xb = s_xb + w * kXbuf3;
+            const float4 *gk = G + (d.vec_off + (long long)k * d.Nnc * spc + s) * kVec3;
+            // The thirds of the spectra go one after another through product and
+            // 512-point transform; each third's spectra are loaded while the third
+            // before it is transformed (the last one's while the next block's first
+            // third is).  The block spectrum is re-read for every PRN of the tile
+            // (L1/L2 hits after the first) rather than pinned in registers.
+            f4v gl[2][4];
+            auto load = [&](const float4 *gp, int zero, auto cc) {
+                constexpr int c = decltype(cc)::value;
+                // a scalar base (uniform over the wave) and the lane's 32-bit offset
+                const GNSS_GLOBAL f4v *gq = (const GNSS_GLOBAL f4v *)uniform64((long long)(gp + zero));
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) gl[i][q] = (gq + (i * kSpec3 + (4 * c + q) * 64))[(unsigned)l];
+            };
+            load(gk, 0, std::integral_constant<int, 0>());
             // groups of kSumGroup blocks (one for most requests)
             for (int b0 = 0; b0 < d.Nnc; b0 += kSumGroup) {
-                if (b0) add_group<PT>(acc, d, ptile, k, s, l, 0x1p-46f, d.acc || b0 > kSumGroup);
-                const float4 *gk = G + (d.vec_off + ((long long)k * d.Nnc + b0) * spc + s) * kVec;
-                const int nb = min(d.Nnc - b0, kSumGroup);
-                for (int b = 0; b < nb; ++b) {
-                    const float4 *gp = gk + (long long)b * spc * kVec;
+                if (b0) add_group<PT>(acc, d, ptile, k, s, l, kScale, d.acc || b0 > kSumGroup);
+                const int b1 = min(d.Nnc, b0 + kSumGroup);
+                for (int b = b0; b < b1; ++b, gk += (long long)spc * kVec3) {
                     // PRN slots past n_prn hold the all-zero spectrum of row 0; they are
                     // computed (no branch in the loop) but never written.
 #pragma unroll
                     for (int p = 0; p < PT; ++p) {
-                        // the block spectrum is re-read for every PRN of the tile (L1/L2
-                        // hits after the first) rather than pinned in registers
-                        float2 z[32];
-                        // (the cast keeps them global loads: the compiler cannot tell
-                        // behind the opaque pointer, and flat loads wait with the LDS)
-                        const float4 *gv = gp;
-                        asm volatile("" : "+v"(gv));
-                        const GNSS_GLOBAL f4v *gq = (const GNSS_GLOBAL f4v *)gv;
-                        phase_barrier();
+                        float2 v[3][8];
+                        auto third = [&](auto c3) {
+                            constexpr int c = decltype(c3)::value;
+                            constexpr int S1 = 2 * kSeg3 + 1;
+                            const float2 *cc = s_cc + p * kCodeLds3 + l;
+                            const float2 *cm = s_cc + p * kCodeLds3 + 2 * kSeg3 - l;  // mirrored
+                            // z[n] = G_0 conj(C_0) + G_1 conj(C_1) and the first stage of the
+                            // radix-8 pass: z[n + 4]'s products are added onto z[n], and
+                            // z[n] - z[n + 4] = 2 z[n] - (z[n] + z[n + 4])
+                            float2 sm[4], df[4];
 #pragma unroll
-                        for (int jj = 0; jj < 16; ++jj) {
-                            const f4v t = gq[jj * 64 + l];
-                            const float4 c = s_cc[p * kVec + jj * 64 + l];
-                            z[2 * jj] = c_mul(make_float2(t.x, t.y), make_float2(c.x, c.y));
-                            z[2 * jj + 1] = c_mul(make_float2(t.z, t.w), make_float2(c.z, c.w));
-                        }
-                        phase_barrier();
-                        ifft2048<true, true>(z, xb, s_tw, s_tw + kT1Elems, l);
-                        phase_barrier();
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-#pragma unroll
-                            for (int k2b = 0; k2b < 4; ++k2b) {
-                                float2 rv = z[8 * u + k2b];
-                                acc[p][4 * u + k2b] = fmaf(rv.x, rv.x, fmaf(rv.y, rv.y, acc[p][4 * u + k2b]));
+                            for (int n = 0; n < 4; ++n) {
+                                const f4v a0 = gl[0][n / 2], a1 = gl[1][n / 2], b0 = gl[0][n / 2 + 2], b1 = gl[1][n / 2 + 2];
+                                const int e = 2 * (n & 1);
+                                const float2 g0 = make_float2(a0[e], a0[e + 1]), g1 = make_float2(a1[e], a1[e + 1]);
+                                const float2 h0 = make_float2(b0[e], b0[e + 1]), h1 = make_float2(b1[e], b1[e + 1]);
+                                float2 z;
+                                if constexpr (c < 2) {
+                                    z = c_mul_add(g1, cc[S1 + kSeg3 * c + 64 * n], c_mul(g0, cc[kSeg3 * c + 64 * n]));
+                                    sm[n] = c_mul_add(h1, cc[S1 + kSeg3 * c + 64 * (n + 4)],
+                                                      c_mul_add(h0, cc[kSeg3 * c + 64 * (n + 4)], z));
+                                } else {
+                                    z = c_mulc_add(g1, cm[S1 - 64 * n], c_mulc(g0, cm[-64 * n]));
+                                    sm[n] = c_mulc_add(h1, cm[S1 - 64 * (n + 4)], c_mulc_add(h0, cm[-64 * (n + 4)], z));
+                                }
+                                df[n] = make_float2(fmaf(2.f, z.x, -sm[n].x), fmaf(2.f, z.y, -sm[n].y));
+                                if (n & 1) phase_barrier();  // bounds the code values in flight
                             }
+                            // the products before the loads that take over their registers
+                            int zero = 0;
+                            asm volatile("" : "+s"(zero), "+v"(sm[0].x), "+v"(sm[0].y), "+v"(sm[1].x), "+v"(sm[1].y),
+                                         "+v"(sm[2].x), "+v"(sm[2].y), "+v"(sm[3].x), "+v"(sm[3].y), "+v"(df[0].x),
+                                         "+v"(df[0].y), "+v"(df[1].x), "+v"(df[1].y), "+v"(df[2].x), "+v"(df[2].y),
+                                         "+v"(df[3].x), "+v"(df[3].y));
+                            if constexpr (c < 2)
+                                load(gk, zero, std::integral_constant<int, c + 1>());
+                            else if (p + 1 < PT)
+                                load(gk, zero, std::integral_constant<int, 0>());
+                            else  // (after the last block its own again: no branch around the loads)
+                                load(gk + (b + 1 < d.Nnc ? (long long)spc * kVec3 : 0), zero,
+                                     std::integral_constant<int, 0>());
+                            phase_barrier();
+                            dft8_rest<true>(sm, df, v[c]);
+                            ifft512_rest(v[c], xb, lw, l);
+                            if constexpr (c < 2) phase_barrier();
+                        };
+                        unrolled<3>(third);
+                        lags3(v, lw, [&](int j, float2 o) { acc[p][j] = fmaf(o.x, o.x, fmaf(o.y, o.y, acc[p][j])); });
+                        phase_barrier();
                     }
                 }
             }
         }
 
-        store_tile<PT, W>(acc, s_stage, d, ptile, chunk, w, l, tid, 0x1p-46f, d.acc || d.Nnc > kSumGroup);
+        store_tile<PT, W, true>(acc, s_stage, d, ptile, chunk, w, l, tid, kScale, d.acc || d.Nnc > kSumGroup);
     }
 }
 
@@ -1096,7 +1346,7 @@ __global__ __launch_bounds__(64 * kCorrWavesH) __attribute__((amdgpu_waves_per_e
             }
         }
 
-        store_tile<PT, W>(acc, s_stage, d, ptile, chunk, w, l, tid, out_scale, d.acc != 0);
+        store_tile<PT, W, false>(acc, s_stage, d, ptile, chunk, w, l, tid, out_scale, d.acc != 0);
     }
 }
 
@@ -2348,16 +2598,6 @@ __device__ __forceinline__ float2 twiddle16(float2 v, int a, bool inv)
     }
 }
 
-// f(std::integral_constant<int, i>()) for i < N, in order
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void unrolled(F &&f)
-{
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>());
-        unrolled<N, I + 1>(f);
-    }
-}
-
 // a copy the compiler cannot see through (keeps per-column products from
 // being hoisted out of loops and held)
 __device__ __forceinline__ float2 opaque(float2 v)
@@ -3135,8 +3375,7 @@ hipError_t launch_batch(const Launch &L, const Tables &T, int2 *d_F, void *d_G, 
                         float *d_part, int n_cu, hipStream_t s, hipEvent_t *marks)
 {
     const uint32_t *d_lut = T.lut;
-    const float2 *d_tw = T.tw;
-    const float4 *d_cs = T.cs;
+    const void *d_cs = T.cs;
     const bool h = L.precision == GNSS_FP16, x = L.precision == GNSS_FP16_PFA;
     // FP16 modes: packed spectra, then the per-vector exponents
     uint4 *d_Gh = (uint4 *)d_G;
@@ -3151,6 +3390,12 @@ hipError_t launch_batch(const Launch &L, const Tables &T, int2 *d_F, void *d_G, 
     if ((e = mark(0)) != hipSuccess) return e;
     if (x && L.fd) {
         if ((e = launch_fd(L, T, d_F, d_G, d_E, n_cu, s)) != hipSuccess) return e;
+    } else if (!x && !h) {
+        if (L.total[kStBoxFft] > 0) {
+            hipLaunchKernelGGL(k_box_fft, dim3((unsigned)std::min(L.total[kStBoxFft], 0x7fffffffLL)), dim3(kBfThreads),
+                               0, s, L.reqs, L.hdr, L.pre, d_lut, T.tw_gen, (float4 *)d_G);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        }
     } else if (L.total[kStBox] > 0) {
         static int cap = 0;
         if (!cap) cap = occupancy(k_box, 256, n_cu);
@@ -3167,13 +3412,7 @@ hipError_t launch_batch(const Launch &L, const Tables &T, int2 *d_F, void *d_G, 
         hipLaunchKernelGGL(k_fft_x, dim3(grid_for((L.total[kStVec] + 3) / 4, cap, false)), dim3(256), 0, s, d_F,
                            (const pfa::u4 *)T.frags_x, (pfa::u4 *)d_G, d_E, L.hdr);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-    } else if (L.total[kStVec] > 0 && !h) {
-        static int cap = 0;
-        if (!cap) cap = occupancy(k_fft_poly, 256, n_cu);
-        hipLaunchKernelGGL(k_fft_poly, dim3(grid_for((L.total[kStVec] + 3) / 4, cap, false)), dim3(256), 0,
-                           s, d_F, d_tw, (float4 *)d_G, L.hdr);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    } else if (L.total[kStVec] > 0) {
+    } else if (L.total[kStVec] > 0 && h) {
         static int cap = 0;
         if (!cap) cap = occupancy(k_fft_poly_h, 256, n_cu);
         hipLaunchKernelGGL(k_fft_poly_h, dim3(grid_for((L.total[kStVec] + 7) / 8, cap, false)), dim3(256), 0,
@@ -3273,27 +3512,27 @@ hipError_t launch_batch(const Launch &L, const Tables &T, int2 *d_F, void *d_G, 
             static int cap = 0;
             if (!cap) cap = occupancy(k_corr<1, 4, 3>, 64 * 4, n_cu);
             hipLaunchKernelGGL((k_corr<1, 4, 3>), dim3(grid_for(L.total[kStCorr], cap, pers)), dim3(64 * 4), 0, s,
-                               L.reqs, L.hdr, L.pre, (const float4 *)d_G, d_cs, d_tw);
+                               L.reqs, L.hdr, L.pre, (const float4 *)d_G, (const float2 *)d_cs, T.tw_gen);
         } else if (L.corr_pt == 1 && L.corr_w == 6) {
             static int cap = 0;
             if (!cap) cap = occupancy(k_corr<1, 6, 3>, 64 * 6, n_cu);
             hipLaunchKernelGGL((k_corr<1, 6, 3>), dim3(grid_for(L.total[kStCorr], cap, pers)), dim3(64 * 6), 0, s,
-                               L.reqs, L.hdr, L.pre, (const float4 *)d_G, d_cs, d_tw);
+                               L.reqs, L.hdr, L.pre, (const float4 *)d_G, (const float2 *)d_cs, T.tw_gen);
         } else if (L.corr_pt == 1) {
             static int cap = 0;
             if (!cap) cap = occupancy(k_corr<1, 12, 3>, 64 * 12, n_cu);
             hipLaunchKernelGGL((k_corr<1, 12, 3>), dim3(grid_for(L.total[kStCorr], cap, pers)), dim3(64 * 12), 0, s,
-                               L.reqs, L.hdr, L.pre, (const float4 *)d_G, d_cs, d_tw);
+                               L.reqs, L.hdr, L.pre, (const float4 *)d_G, (const float2 *)d_cs, T.tw_gen);
         } else if (L.corr_pt == 2) {
             static int cap = 0;
             if (!cap) cap = occupancy(k_corr<2, kCorrWaves, 2>, 64 * kCorrWaves, n_cu);
             hipLaunchKernelGGL((k_corr<2, kCorrWaves, 2>), dim3(grid_for(L.total[kStCorr], cap, pers)),
-                               dim3(64 * kCorrWaves), 0, s, L.reqs, L.hdr, L.pre, (const float4 *)d_G, d_cs, d_tw);
+                               dim3(64 * kCorrWaves), 0, s, L.reqs, L.hdr, L.pre, (const float4 *)d_G, (const float2 *)d_cs, T.tw_gen);
         } else {
             static int cap = 0;
             if (!cap) cap = occupancy(k_corr<4, kCorrWaves, 2>, 64 * kCorrWaves, n_cu);
             hipLaunchKernelGGL((k_corr<4, kCorrWaves, 2>), dim3(grid_for(L.total[kStCorr], cap, pers)),
-                               dim3(64 * kCorrWaves), 0, s, L.reqs, L.hdr, L.pre, (const float4 *)d_G, d_cs, d_tw);
+                               dim3(64 * kCorrWaves), 0, s, L.reqs, L.hdr, L.pre, (const float4 *)d_G, (const float2 *)d_cs, T.tw_gen);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
