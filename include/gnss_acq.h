@@ -430,10 +430,10 @@ typedef struct gnss_track_request {
 int gnss_track(const gnss_track_request *req);
 
 /* Tracking correlators of n_req requests (device samples and outputs) in one
- * launch, one workgroup per (request, epoch), enqueued on `stream` (NULL =
- * the HIP null stream); returns without waiting.  Calls on one context must
- * not overlap on different streams.  Errors: as gnss_track; a bad request
- * reports its index. */
+ * launch, one workgroup per (request, epoch, four channels), enqueued on
+ * `stream` (NULL = the HIP null stream); returns without waiting.  Calls on one
+ * context must not overlap on different streams.  Errors: as gnss_track; a bad
+ * request reports its index. */
 int gnss_track_device(gnss_ctx *ctx, const gnss_track_request *reqs, int32_t n_req, void *stream);
 
 /* ---- per-stage device timing -------------------------------------------- */

@@ -3559,7 +3559,6 @@ hipError_t launch_batch(const Launch &L, const Tables &T, int2 *d_F, void *d_G, 
 // mixing stage and time-domain correlation, Fig. 3): early / prompt / late
 // sums per (request, channel, epoch), exact in integers.
 // ===========================================================================
-constexpr long long kCodeFix = 1023LL << 32;  // one code period, chips * 2^32
 
 // One round of the wave reduce-scatter below: value i pairs with value
 // i + H; the lane whose bit O is set keeps the upper one, its partner the
@@ -3576,7 +3575,7 @@ __device__ __forceinline__ void rs_round(long long (&v)[24], int l)
     }
 }
 
-// The workgroup's sums of a pass's kTrackCG x 6 per-thread totals, with one
+// The workgroup's sums of kTrackCG x 6 per-thread sums, with one
 // pair of barriers for all of them.  Within a wave a reduce-scatter halves
 // the values per lane each round (24, 12, 6, 3, padded to 4, 2, 1) while
 // the lanes paired across bits 5 .. 1 add them, and the last round over bit
@@ -3586,14 +3585,14 @@ __device__ __forceinline__ void rs_round(long long (&v)[24], int l)
 // order does not matter.
 constexpr int kTrackVals = kTrackCG * 6;
 static_assert(kTrackVals == 24, "the reduce-scatter rounds are laid out for 24 values");
-__device__ __forceinline__ long long block_sums64(const long long (&tot)[kTrackCG][6], long long *s_red)
+__device__ __forceinline__ long long block_sums64(const int (&acc)[kTrackCG][6], long long *s_red)
 {
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     long long v[24];
 #pragma unroll
     for (int cc = 0; cc < kTrackCG; ++cc)
 #pragma unroll
-        for (int k = 0; k < 6; ++k) v[cc * 6 + k] = tot[cc][k];
+        for (int k = 0; k < 6; ++k) v[cc * 6 + k] = acc[cc][k];
     rs_round<32, 12>(v, l);
     rs_round<16, 6>(v, l);
     rs_round<8, 3>(v, l);
@@ -3617,122 +3616,147 @@ __device__ __forceinline__ long long block_sums64(const long long (&tot)[kTrackC
 // early (chip in [0, 1023]) and late (chip in [-1, 1022]) lookups need no wrap.
 constexpr int kSignRow = 1028;
 
-// Correlates the epoch's samples of one thread with kTrackCG channels:
-// FMT-specialised so the sample decode leaves the loop.  All products fit in
-// 24 bits (|x| <= 127, |LUT| <= 4096, |y| < 2^20), so 24-bit multiplies are exact.
-template <int FMT>
-__device__ __forceinline__ void track_pass(const void *samples, long long n_first, int n_mine,
-                                           const uint32_t *s_lut, const int8_t (*s_sign)[kSignRow],
-                                           uint32_t (&ph)[kTrackCG], const uint32_t (&dph)[kTrackCG],
-                                           unsigned long long (&q)[kTrackCG],
-                                           const unsigned long long (&dq)[kTrackCG],
-                                           const unsigned long long (&dl)[kTrackCG],
-                                           const unsigned long long (&ndl)[kTrackCG], long long (&tot)[kTrackCG][6])
+// A code phase of less than two periods, brought below one period: the period
+// has a zero low word, so only the chip number takes part, and of hi and hi -
+// 1023 (mod 2^32) the smaller one is right.
+__device__ __forceinline__ unsigned long long code_wrap(unsigned long long q)
 {
-    // int32 partial sums over at most 1024 samples: |x y| < 2^20
-    for (int j0 = 0; j0 < n_mine; j0 += 1024) {
-        int acc[kTrackCG][6];
+    const uint32_t hi = (uint32_t)(q >> 32);
+    return ((unsigned long long)min(hi, hi - (uint32_t)kCodeLen) << 32) | (uint32_t)q;
+}
+
+// Correlates the workgroup's epoch with kTrackCG channels, FMT-specialised so
+// that the sample decode leaves the loop; returns value i's sum in thread i <
+// kTrackVals.  p is the byte of the epoch's first sample (the same pointer in
+// every thread), off the thread's offset from it.  qe, ql: early and late
+// offsets, one chip more (the sign rows start at chip -1).  Mixing is two dot
+// products per channel (mix_add); |y| < 2^20, so the 24-bit multiply-adds by
+// the +-1 chips are exact and int32 holds the sums of 1024 samples; longer
+// epochs are summed over the workgroup in parts.
+template <int FMT>
+__device__ __forceinline__ long long track_pass(const GNSS_GLOBAL uint8_t *p, uint32_t off, int epoch_len,
+                                                const uint2 *s_lut, const int8_t (*s_sign)[kSignRow],
+                                                long long *s_red, uint32_t (&ph)[kTrackCG],
+                                                const uint32_t (&dph)[kTrackCG], unsigned long long (&q)[kTrackCG],
+                                                const unsigned long long (&dq)[kTrackCG],
+                                                const unsigned long long (&qe)[kTrackCG],
+                                                const unsigned long long (&ql)[kTrackCG])
+{
+    constexpr int kStep = FMT == GNSS_CPLX_I8 ? 2 * kTrackThreads
+                          : FMT == GNSS_REAL_I8 ? kTrackThreads
+                                                : kTrackThreads / 4;  // bytes of 256 samples
+    const int n_full = epoch_len / kTrackThreads;  // samples of every thread; one more below the remainder
+    int acc[kTrackCG][6];
+    auto sample = [&](s2v x) {
+#pragma unroll
+        for (int cc = 0; cc < kTrackCG; ++cc) {
+            // mix_add onto 0; in asm, as the builtin takes the form that adds in
+            // place and needs its accumulators cleared (and so that the compiler does
+            // not distribute the +-1 factors below into the products)
+            const uint2 e = s_lut[ph[cc] >> 22];
+            int yr, yi;
+            asm("v_dot2_i32_i16 %0, %1, %2, 0" : "=v"(yr) : "v"(x), "v"(e.x));
+            asm("v_dot2_i32_i16 %0, %1, %2, 0" : "=v"(yi) : "v"(x), "v"(e.y));
+            const int8_t *row = s_sign[cc];
+            const int se = row[(uint32_t)((q[cc] + qe[cc]) >> 32)], sp = row[(uint32_t)(q[cc] >> 32) + 1];
+            const int sl = row[(uint32_t)((q[cc] + ql[cc]) >> 32)];
+            acc[cc][0] += __mul24(se, yr);
+            acc[cc][1] += __mul24(se, yi);
+            acc[cc][2] += __mul24(sp, yr);
+            acc[cc][3] += __mul24(sp, yi);
+            acc[cc][4] += __mul24(sl, yr);
+            acc[cc][5] += __mul24(sl, yi);
+            ph[cc] += dph[cc];
+            q[cc] = code_wrap(q[cc] + dq[cc]);
+        }
+    };
+    long long total = 0;
+    int j = 0;
+    do {
 #pragma unroll
         for (int cc = 0; cc < kTrackCG; ++cc)
 #pragma unroll
             for (int k = 0; k < 6; ++k) acc[cc][k] = 0;
-        const int j1 = min(n_mine, j0 + 1024);
-        for (int j = j0; j < j1; ++j) {
-            int xr, xi;
-            load_sample(samples, FMT, n_first + (long long)j * kTrackThreads, xr, xi);
-#pragma unroll
-            for (int cc = 0; cc < kTrackCG; ++cc) {
-                const uint32_t lv = s_lut[ph[cc] >> 22];
-                const int cs = (int)(int16_t)(lv & 0xFFFFu), sn = (int)(int16_t)(lv >> 16);
-                int yr, yi;
-                if (FMT == GNSS_CPLX_I8) {
-                    yr = __mul24(xr, cs) + __mul24(xi, sn);
-                    yi = __mul24(xi, cs) - __mul24(xr, sn);
-                } else {
-                    yr = __mul24(xr, cs);
-                    yi = __mul24(-xr, sn);
-                }
-                // keeps the compiler from distributing the +-1 factors below into these
-                // products (which it then evaluates with 64-bit multiply-adds)
-                asm volatile("" : "+v"(yr), "+v"(yi));
-                const int chp = (int)(uint32_t)(q[cc] >> 32);
-                const int che = (int)(uint32_t)((q[cc] + dl[cc]) >> 32);
-                const int chl = (int)(uint32_t)((q[cc] + ndl[cc]) >> 32);  // high word of q - dl: >= -1
-                const int se = s_sign[cc][che + 1], sp = s_sign[cc][chp + 1], sl = s_sign[cc][chl + 1];
-                acc[cc][0] += __mul24(se, yr);
-                acc[cc][1] += __mul24(se, yi);
-                acc[cc][2] += __mul24(sp, yr);
-                acc[cc][3] += __mul24(sp, yi);
-                acc[cc][4] += __mul24(sl, yr);
-                acc[cc][5] += __mul24(sl, yi);
-                ph[cc] += dph[cc];
-                q[cc] += dq[cc];
-                q[cc] -= q[cc] >= (unsigned long long)kCodeFix ? (unsigned long long)kCodeFix : 0ull;
-            }
-        }
-#pragma unroll
-        for (int cc = 0; cc < kTrackCG; ++cc)
-#pragma unroll
-            for (int k = 0; k < 6; ++k) tot[cc][k] += acc[cc][k];
-    }
+        const int j1 = min(n_full, j + 1023);
+        for (; j < j1; ++j) sample(load_mix<FMT>(p + (long long)j * kStep, off));  // packed: off counts samples
+        if (j == n_full && (int)threadIdx.x < epoch_len - n_full * kTrackThreads)
+            sample(load_mix<FMT>(p + (long long)j * kStep, off));
+        total += block_sums64(acc, s_red);
+    } while (j < n_full);
+    return total;
 }
 
-// One workgroup per (request, epoch); the request's channels in passes of
-// kTrackCG.  Thread t handles samples t, t + 256, ... of the epoch with the
-// NCO words advanced by 256 steps between them; the code phase is kept in
-// [0, 1023 * 2^32), which leaves every chip index mod 1023 unchanged.
+// One workgroup per (request, epoch, group of kTrackCG channels); the groups of
+// an epoch are neighbours on one XCD, whose L2 holds the epoch's samples.
+// Thread t handles samples t, t + 256, ... of the epoch with the NCO words
+// advanced by 256 steps between them; the code phase is kept in [0, 1023 *
+// 2^32), which leaves every chip index mod 1023 unchanged.  Bound: integer
+// vector issue, 67 instructions per sample and four channels (133 with byte
+// extraction and products, 64-bit compares and borrows), at five waves per SIMD
+// (96 VGPRs; 144 and three when int64 totals were held beside the int32 sums).
+// 32 records x 12 channels x 100 epochs of 1 ms at 16.368 MHz: 0.60 -> 0.36 ms
+// (1.05 -> 1.75 10^12 sample-channels/s); one record x 10 channels x 20 epochs
+// at 4.092 MHz: 35 -> 12 us, its three groups side by side instead of one after
+// another.
 __global__ __launch_bounds__(kTrackThreads) void k_track(const TrackDesc *__restrict__ R, const long long *pre,
                                                          int n_req, long long total, const TrackCh *__restrict__ CH,
                                                          const uint8_t *codes, const uint32_t *lut)
 {
-    __shared__ uint32_t s_lut[1024];
+    __shared__ uint2 s_lut[1024];
     __shared__ int8_t s_sign[kTrackCG][kSignRow];
     __shared__ long long s_red[kTrackThreads / 64 * kTrackVals];
-    for (int i = threadIdx.x; i < 1024; i += kTrackThreads) s_lut[i] = lut[i];
-    for (long long it = blockIdx.x; it < total; it += gridDim.x) {
+    const int tid = threadIdx.x;
+    stage_mix_lut(s_lut, lut, tid, kTrackThreads);
+    for (long long it = xcd_remap(blockIdx.x, gridDim.x); it < total; it += gridDim.x) {
         const int r = find_req(pre, n_req, it);
         const TrackDesc &d = R[r];
-        const int e = (int)(it - pre[r]);
-        const long long n_first = d.start + (long long)e * d.epoch_len + threadIdx.x;
-        for (int c0 = 0; c0 < d.n_ch; c0 += kTrackCG) {
-            __syncthreads();  // LUT staged; previous pass done with s_sign and s_red
-            for (int i = threadIdx.x; i < kTrackCG * (kCodeLen + 2); i += kTrackThreads) {
-                const int cc = i / (kCodeLen + 2), k = i - cc * (kCodeLen + 2);
-                const int prn = CH[d.ch_off + min(c0 + cc, d.n_ch - 1)].prn;
+        const int groups = (d.n_ch + kTrackCG - 1) / kTrackCG;
+        const long long local = it - pre[r];
+        const int e = (int)(local / groups), c0 = (int)(local - (long long)e * groups) * kTrackCG;
+        const long long n_e = d.start + (long long)e * d.epoch_len;  // the epoch's first sample
+        __syncthreads();  // table staged; previous item done with s_sign and s_red
+#pragma unroll
+        for (int cc = 0; cc < kTrackCG; ++cc) {
+            const uint8_t *code = codes + CH[d.ch_off + min(c0 + cc, d.n_ch - 1)].prn * kCodeLen;
+            for (int k = tid; k < kCodeLen + 2; k += kTrackThreads) {
                 const int chip = k == 0 ? kCodeLen - 1 : (k == kCodeLen + 1 ? 0 : k - 1);
-                s_sign[cc][k] = (int8_t)(1 - 2 * (int)(codes[prn * kCodeLen + chip] & 1u));
+                s_sign[cc][k] = (int8_t)(1 - 2 * (int)(code[chip] & 1u));
             }
-            __syncthreads();
-            uint32_t ph[kTrackCG], dph[kTrackCG];
-            unsigned long long q[kTrackCG], dq[kTrackCG], dl[kTrackCG], ndl[kTrackCG];
+        }
+        uint32_t ph[kTrackCG], dph[kTrackCG];
+        unsigned long long q[kTrackCG], dq[kTrackCG], qe[kTrackCG], ql[kTrackCG];
 #pragma unroll
-            for (int cc = 0; cc < kTrackCG; ++cc) {
-                const TrackCh c = CH[d.ch_off + min(c0 + cc, d.n_ch - 1)];
-                ph[cc] = c.phi0 + (uint32_t)((unsigned long long)n_first * c.D);
-                dph[cc] = (uint32_t)kTrackThreads * c.D;
-                q[cc] = (unsigned long long)(c.q0 + n_first * c.R) % (unsigned long long)kCodeFix;
-                dq[cc] = (unsigned long long)((long long)kTrackThreads * c.R) % (unsigned long long)kCodeFix;
-                dl[cc] = (unsigned long long)c.dl;
-                ndl[cc] = (unsigned long long)(-c.dl);
-            }
-            long long tot[kTrackCG][6];
-#pragma unroll
-            for (int cc = 0; cc < kTrackCG; ++cc)
-#pragma unroll
-                for (int k = 0; k < 6; ++k) tot[cc][k] = 0;
-            const int n_mine = d.epoch_len > (int)threadIdx.x ? (d.epoch_len - 1 - (int)threadIdx.x) / kTrackThreads + 1 : 0;
-            if (d.fmt == GNSS_CPLX_I8)
-                track_pass<GNSS_CPLX_I8>(d.samples, n_first, n_mine, s_lut, s_sign, ph, dph, q, dq, dl, ndl, tot);
-            else if (d.fmt == GNSS_REAL_I8)
-                track_pass<GNSS_REAL_I8>(d.samples, n_first, n_mine, s_lut, s_sign, ph, dph, q, dq, dl, ndl, tot);
-            else
-                track_pass<GNSS_REAL_2BIT_PACKED>(d.samples, n_first, n_mine, s_lut, s_sign, ph, dph, q, dq, dl, ndl,
-                                                  tot);
-            const long long v = block_sums64(tot, s_red);
-            if (threadIdx.x < kTrackVals) {
-                const int cc = threadIdx.x / 6, k = threadIdx.x - cc * 6;
-                if (c0 + cc < d.n_ch) gmem(d.out)[((long long)(c0 + cc) * d.n_epochs + e) * 6 + k] = v;
-            }
+        for (int cc = 0; cc < kTrackCG; ++cc) {
+            const TrackCh c = CH[d.ch_off + min(c0 + cc, d.n_ch - 1)];
+            ph[cc] = c.phi0 + (uint32_t)((unsigned long long)(n_e + tid) * c.D);
+            dph[cc] = (uint32_t)kTrackThreads * c.D;
+            // q0 + n R < 2^62; 256 R is at most one period, so a thread's offset t R is
+            // below one and the step 256 R needs one wrap
+            const unsigned long long q0 = (unsigned long long)(c.q0 + n_e * c.R);
+            const unsigned long long q1 = ((unsigned long long)((uint32_t)(q0 >> 32) % (uint32_t)kCodeLen) << 32) | (uint32_t)q0;
+            q[cc] = code_wrap(q1 + (unsigned long long)(tid * c.R));
+            dq[cc] = code_wrap((unsigned long long)(kTrackThreads * c.R));
+            qe[cc] = (1ull << 32) + (unsigned long long)c.dl;
+            ql[cc] = (1ull << 32) - (unsigned long long)c.dl;
+            // not seen as each other's negatives (two additions, not an addition and a
+            // subtraction with its borrow)
+            asm volatile("" : "+s"(ql[cc]));
+        }
+        __syncthreads();
+        const GNSS_GLOBAL uint8_t *p = (const GNSS_GLOBAL uint8_t *)d.samples;
+        long long v;
+        if (d.fmt == GNSS_CPLX_I8)
+            v = track_pass<GNSS_CPLX_I8>(p + 2 * n_e, 2u * (uint32_t)tid, d.epoch_len, s_lut, s_sign, s_red, ph, dph, q,
+                                         dq, qe, ql);
+        else if (d.fmt == GNSS_REAL_I8)
+            v = track_pass<GNSS_REAL_I8>(p + n_e, (uint32_t)tid, d.epoch_len, s_lut, s_sign, s_red, ph, dph, q, dq, qe,
+                                         ql);
+        else
+            v = track_pass<GNSS_REAL_2BIT_PACKED>(p + (n_e >> 2), (uint32_t)(n_e & 3) + (uint32_t)tid, d.epoch_len,
+                                                  s_lut, s_sign, s_red, ph, dph, q, dq, qe, ql);
+        if (tid < kTrackVals) {
+            const int cc = tid / 6, k = tid - cc * 6;
+            if (c0 + cc < d.n_ch) gmem(d.out)[((long long)(c0 + cc) * d.n_epochs + e) * 6 + k] = v;
         }
     }
 }

@@ -104,7 +104,8 @@ static int track_enqueue(gnss_ctx *c, Workspace &w, const gnss_track_request *re
             std::string m = t_err;
             return set_err(rc, "request %d: %s", i, m.c_str());
         }
-        pre[i + 1] = pre[i] + r.n_epochs;
+        // a work item per epoch and group of channels
+        pre[i + 1] = pre[i] + (long long)r.n_epochs * ((r.n_channels + gnss::kTrackCG - 1) / gnss::kTrackCG);
     }
     const size_t off_pre = align256((size_t)n * sizeof(gnss::TrackDesc));
     const size_t off_ch = off_pre + align256((size_t)(n + 1) * sizeof(long long));
