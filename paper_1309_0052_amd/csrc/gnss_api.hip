@@ -480,17 +480,23 @@ int stage_batch(gnss_ctx *c, Workspace &w, BatchHost &B, hipStream_t s, gnss::La
         B.d[r].dk = (const uint32_t *)(dm + ml.dk) + B.dk_off[r];
         B.d[r].cshift = B.cshift_off[r] >= 0 ? (const int32_t *)(dm + ml.cshift) + B.cshift_off[r] : nullptr;
     }
-    // pinned staging: wait until the previous copy out of it has finished
-    if (w.stage_ev) HIP_TRY(hipEventSynchronize(w.stage_ev));
-    if (w.h_stage_cap < mb) {
-        if (w.h_stage) HIP_TRY(hipHostFree(w.h_stage));
-        w.h_stage = nullptr;
-        w.h_stage_cap = 0;
-        HIP_TRY(hipHostMalloc(&w.h_stage, mb, hipHostMallocDefault));
-        w.h_stage_cap = mb;
+    unsigned char *h;
+    const bool by_arg = mb <= gnss::kMetaArgBytes && !w.staged_meta;
+    if (by_arg) {
+        h = w.meta_arg;
+    } else {
+        // pinned staging: wait until the previous copy out of it has finished
+        if (w.stage_ev) HIP_TRY(hipEventSynchronize(w.stage_ev));
+        if (w.h_stage_cap < mb) {
+            if (w.h_stage) HIP_TRY(hipHostFree(w.h_stage));
+            w.h_stage = nullptr;
+            w.h_stage_cap = 0;
+            HIP_TRY(hipHostMalloc(&w.h_stage, mb, hipHostMallocDefault));
+            w.h_stage_cap = mb;
+        }
+        if (!w.stage_ev) HIP_TRY(hipEventCreateWithFlags(&w.stage_ev, hipEventDisableTiming));
+        h = (unsigned char *)w.h_stage;
     }
-    if (!w.stage_ev) HIP_TRY(hipEventCreateWithFlags(&w.stage_ev, hipEventDisableTiming));
-    unsigned char *h = (unsigned char *)w.h_stage;
     memset(h, 0, mb);
     gnss::BatchHdr hdr{};
     hdr.n_req = B.n;
@@ -501,8 +507,13 @@ int stage_batch(gnss_ctx *c, Workspace &w, BatchHost &B, hipStream_t s, gnss::La
     memcpy(h + ml.desc, B.d.data(), (size_t)B.n * sizeof(gnss::ReqDesc));
     if (!B.dk.empty()) memcpy(h + ml.dk, B.dk.data(), B.dk.size() * sizeof(uint32_t));
     if (!B.cshift.empty()) memcpy(h + ml.cshift, B.cshift.data(), B.cshift.size() * sizeof(int32_t));
-    HIP_TRY(hipMemcpyAsync(w.meta.p, h, mb, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipEventRecord(w.stage_ev, s));
+    if (by_arg) {
+        HIP_TRY(gnss::launch_meta(h, mb, w.meta.p, s));
+    } else {
+        HIP_TRY(hipMemcpyAsync(w.meta.p, h, mb, hipMemcpyHostToDevice, s));
+        HIP_TRY(hipEventRecord(w.stage_ev, s));
+    }
+    L.fresh = 1;
     L.hdr = (gnss::BatchHdr *)dm;
     L.pre = (const long long *)(dm + ml.pre);
     L.reqs = (const gnss::ReqDesc *)(dm + ml.desc);
@@ -1220,6 +1231,7 @@ int gnss_graph_create(gnss_ctx *ctx, const gnss_request *reqs, int32_t n_req, gn
     }
     gnss::Launch L;
     // allocate and fill everything before capture (no allocation inside it)
+    gr->ws.staged_meta = true;
     rc = stage_batch(ctx, gr->ws, B, cs, L);
     if (!rc) {
         e = hipStreamSynchronize(cs);

@@ -211,7 +211,7 @@ struct ReqDesc {
 };
 
 // Batch header (device memory): request count, work totals per stage and the
-// dynamic work counters (zeroed by k_reset at the start of every batch).
+// dynamic work counters (zero as staged; zeroed by k_reset before another use).
 struct BatchHdr {
     int n_req;
     int corr_pt;
@@ -231,6 +231,7 @@ struct Launch {
     int precision;                // GNSS_FP32 / GNSS_FP16 / GNSS_FP16_PFA
     int fd;                       // 1: frequency-domain Doppler (exact-length contexts)
     int nav_pairs;                // 1: navigation-bit hypotheses (exact-length contexts)
+    int fresh;                    // 1: the work counters were cleared with the metadata just staged
     size_t gen_off;               // bytes of the spectrum buffer before its general-rate region
     unsigned gen_pmask, gen_rmask;  // general-rate transform lengths P present (bit P), in one piece and in rows
     unsigned gen_modes;           // and modes: bit 1 M = P, bit 2 two segments, bit 0 even and odd bins
@@ -272,6 +273,11 @@ bool corr_shape_valid(CorrShape c, int precision);
 constexpr int kBoxChunk = 2048;
 constexpr int kPeakThreads = 256;   // threads of the column-max kernel (256-lag blocks)
 constexpr int kArgThreads = 1024;   // threads of the per-PRN argmax kernel
+
+// Metadata of at most kMetaArgBytes to dst (device memory with room to the next
+// multiple of 16 bytes) as a kernel's argument: src may be reused on return.
+constexpr size_t kMetaArgBytes = 3840;  // below the 4 KB of kernel arguments
+hipError_t launch_meta(const void *src, size_t bytes, void *dst, hipStream_t s);
 
 // standalone wipe + fold (stage entry point): request 0 of the staged batch
 hipError_t launch_wipe_fold(const Launch &L, const Plan &p, const uint32_t *d_lut,

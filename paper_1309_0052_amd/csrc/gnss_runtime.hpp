@@ -49,6 +49,9 @@ struct Workspace {
     // buffer waits for it (not for the whole device)
     hipEvent_t use_ev = nullptr;
     bool used = false;
+    // metadata always through the pinned staging (a graph's copy node reads it)
+    bool staged_meta = false;
+    alignas(16) unsigned char meta_arg[gnss::kMetaArgBytes];  // metadata passed as a kernel argument
 };
 
 // A laid-out batch on the host.

@@ -643,6 +643,7 @@ int gnss_autotune(gnss_ctx *ctx, const gnss_request *reqs, int32_t n_req, const 
                     float ms = 0.f;
                     if (hipEventRecord(e0, ctx->stream) != hipSuccess) rc = set_err(GNSS_EDEVICE, "hipEventRecord");
                     if (!rc) rc = launch(ctx, ctx->ws, L, ctx->stream, false);
+                    L.fresh = 0;  // the next run clears the counters itself
                     if (!rc && (hipEventRecord(e1, ctx->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                                 hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
                         rc = set_err(GNSS_EDEVICE, "timing events failed");

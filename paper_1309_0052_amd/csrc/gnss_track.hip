@@ -109,23 +109,34 @@ static int track_enqueue(gnss_ctx *c, Workspace &w, const gnss_track_request *re
     }
     const size_t off_pre = align256((size_t)n * sizeof(gnss::TrackDesc));
     const size_t off_ch = off_pre + align256((size_t)(n + 1) * sizeof(long long));
-    const size_t mb = off_ch + ch.size() * sizeof(gnss::TrackCh);
+    const size_t mb = align256(off_ch + ch.size() * sizeof(gnss::TrackCh));
     if ((rc = ensure_ws(c, w, w.tmeta, mb))) return rc;
-    if (w.stage_ev) HIP_TRY(hipEventSynchronize(w.stage_ev));
-    if (w.h_stage_cap < mb) {
-        if (w.h_stage) HIP_TRY(hipHostFree(w.h_stage));
-        w.h_stage = nullptr;
-        w.h_stage_cap = 0;
-        HIP_TRY(hipHostMalloc(&w.h_stage, mb, hipHostMallocDefault));
-        w.h_stage_cap = mb;
+    unsigned char *h;
+    const bool by_arg = mb <= gnss::kMetaArgBytes;
+    if (by_arg) {
+        h = w.meta_arg;
+    } else {
+        if (w.stage_ev) HIP_TRY(hipEventSynchronize(w.stage_ev));
+        if (w.h_stage_cap < mb) {
+            if (w.h_stage) HIP_TRY(hipHostFree(w.h_stage));
+            w.h_stage = nullptr;
+            w.h_stage_cap = 0;
+            HIP_TRY(hipHostMalloc(&w.h_stage, mb, hipHostMallocDefault));
+            w.h_stage_cap = mb;
+        }
+        if (!w.stage_ev) HIP_TRY(hipEventCreateWithFlags(&w.stage_ev, hipEventDisableTiming));
+        h = (unsigned char *)w.h_stage;
     }
-    if (!w.stage_ev) HIP_TRY(hipEventCreateWithFlags(&w.stage_ev, hipEventDisableTiming));
-    unsigned char *h = (unsigned char *)w.h_stage;
+    memset(h, 0, mb);
     memcpy(h, d.data(), (size_t)n * sizeof(gnss::TrackDesc));
     memcpy(h + off_pre, pre.data(), (size_t)(n + 1) * sizeof(long long));
     memcpy(h + off_ch, ch.data(), ch.size() * sizeof(gnss::TrackCh));
-    HIP_TRY(hipMemcpyAsync(w.tmeta.p, h, mb, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipEventRecord(w.stage_ev, s));
+    if (by_arg) {
+        HIP_TRY(gnss::launch_meta(h, mb, w.tmeta.p, s));
+    } else {
+        HIP_TRY(hipMemcpyAsync(w.tmeta.p, h, mb, hipMemcpyHostToDevice, s));
+        HIP_TRY(hipEventRecord(w.stage_ev, s));
+    }
     unsigned char *dm = (unsigned char *)w.tmeta.p;
     HIP_TRY(gnss::launch_track((const gnss::TrackDesc *)dm, (const long long *)(dm + off_pre), n, pre[n],
                                (const gnss::TrackCh *)(dm + off_ch), c->d_codes, c->d_lut, s));
