@@ -71,7 +71,7 @@ int mark_use(Workspace &w, hipStream_t s)
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     HIP_TRY(hipStreamIsCapturing(s, &st));
     if (st != hipStreamCaptureStatusNone) return GNSS_OK;
-    if (!w.use_ev) HIP_TRY(hipEventCreateWithFlags(&w.use_ev, hipEventDisableTiming));
+    if (!w.use_ev) HIP_TRY(hipEventCreateWithFlags(&w.use_ev, kUseEventFlags));
     HIP_TRY(hipEventRecord(w.use_ev, s));
     w.used = true;
     return GNSS_OK;
@@ -763,7 +763,7 @@ int ctx_init_tables(gnss_ctx *c)
     HIP_TRY(hipHostMalloc(&c->ws_na.h_stage, GNSS_NOALLOC_META_BYTES, hipHostMallocDefault));
     c->ws_na.h_stage_cap = GNSS_NOALLOC_META_BYTES;
     HIP_TRY(hipEventCreateWithFlags(&c->ws_na.stage_ev, hipEventDisableTiming));
-    HIP_TRY(hipEventCreateWithFlags(&c->ws_na.use_ev, hipEventDisableTiming));
+    HIP_TRY(hipEventCreateWithFlags(&c->ws_na.use_ev, kUseEventFlags));
     return GNSS_OK;
 }
 

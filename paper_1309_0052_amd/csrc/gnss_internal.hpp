@@ -273,6 +273,7 @@ bool corr_shape_valid(CorrShape c, int precision);
 constexpr int kBoxChunk = 2048;
 constexpr int kPeakThreads = 256;   // threads of the column-max kernel (256-lag blocks)
 constexpr int kArgThreads = 1024;   // threads of the per-PRN argmax kernel
+constexpr int kPeakLags = 16384;    // column maxima it keeps in registers
 
 // Metadata of at most kMetaArgBytes to dst (device memory with room to the next
 // multiple of 16 bytes) as a kernel's argument: src may be reused on return.

@@ -27,8 +27,8 @@
 //                    (exact int32) + forward FFT of every g_s -> G (storage order)
 //   k_corr           per (PRN tile, Doppler, phase): G * conj(code spectrum),
 //                    IFFT, |.|^2, sum over blocks in registers -> grid
-//   k_colmax/k_peak  column max over Doppler, argmax, second peak, mean
-//   k_interp         FP64 parabolic refinement
+//   k_colmax/k_peak  column max over Doppler, argmax, second peak, mean, FP64
+//                    parabolic refinement
 // FP16 contexts use k_box (the polyphase values to memory, F[k][b][s][1024]),
 // k_fft_poly_h and k_corr_h (packed half precision with per-vector
 // power-of-two scaling).  k_track computes the tracking channel's
@@ -359,6 +359,14 @@ __device__ __forceinline__ int find_req(const long long *pre, int n_req, long lo
     return lo;
 }
 
+// A request's first item.  A single request's is not loaded: that load would
+// stand between the batch's header and the request's fields, a memory latency
+// in each of a search's kernels.
+__device__ __forceinline__ long long first_item(const long long *pre, int n_req, int r)
+{
+    return n_req == 1 ? 0 : pre[r];
+}
+
 // Metadata of small batches as a kernel argument (by value, so the host keeps
 // no staging buffer and waits for nothing): one launch writes it, in place of
 // a copy through the DMA engine and the counters' reset after it.  One
@@ -606,7 +614,7 @@ __global__ __launch_bounds__(256) void k_box(const ReqDesc *__restrict__ R, Batc
         const ReqDesc &d = R[r];
         // (Doppler, block)-major items (dealing them block-major, so that the bins of
         // a block share its samples in L2, was measured 15% slower)
-        const int kb = (int)(it - pst[r]);  // < 2^31 by the plan checks
+        const int kb = (int)(it - first_item(pst, n_req, r));  // < 2^31 by the plan checks
         const int k = kb / d.Nnc, b = kb - (kb / d.Nnc) * d.Nnc;
         box_item<256>(d, k, b, s_lut, s_f, F + (d.vec_off + (long long)kb * d.spc) * kPolyLen);
     }
@@ -704,7 +712,7 @@ __global__ __launch_bounds__(kBfThreads) __attribute__((amdgpu_waves_per_eu(4)))
         const ReqDesc &d = R[r];
         const int N = d.N, spc = d.spc;
         const int parts = bf_parts(spc);
-        const int local = (int)(it - pst[r]);
+        const int local = (int)(it - first_item(pst, n_req, r));
         const int kb = local / parts, part = local - kb * parts;
         const int k = kb / d.Nnc, b = kb - k * d.Nnc;
         const uint32_t D = d.dk[k];
@@ -930,7 +938,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(WPE))) v
         if (it < 0) break;
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
-        const long long local = it - pst[r];
+        const long long local = it - first_item(pst, n_req, r);
         const int ptile = (int)(local % d.n_ptiles), chunk = (int)(local / d.n_ptiles);
         const int item = chunk * W + w;
         const bool active = item < d.n_items;
@@ -1303,7 +1311,7 @@ __global__ __launch_bounds__(64 * kCorrWavesH) __attribute__((amdgpu_waves_per_e
         if (it < 0) break;
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
-        const long long local = it - pst[r];
+        const long long local = it - first_item(pst, n_req, r);
         const int ptile = (int)(local % d.n_ptiles), chunk = (int)(local / d.n_ptiles);
         for (int i = tid; i < NP * 1024; i += 64 * W) {
             const int pp = i >> 10, unit = i & 1023, jj2 = unit >> 6, ll = unit & 63;
@@ -1705,7 +1713,7 @@ __global__ __launch_bounds__(64 * kCorrWavesX) void k_corr_x(const ReqDesc *__re
         if (it < 0) break;
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
-        const long long local = it - pst[r];
+        const long long local = it - first_item(pst, n_req, r);
         const int ptile = (int)(local % d.n_ptiles), chunk = (int)(local / d.n_ptiles);
         const int item = chunk * W + w;
         const bool active = item < d.n_items;
@@ -1947,7 +1955,7 @@ __global__ __launch_bounds__(256) void k_fd_pass1(const ReqDesc *__restrict__ R,
     for (long long it = (long long)blockIdx.x * 4 + w; it < total; it += (long long)gridDim.x * 4) {
         const int r = find_req(pst, n_req, uniform64(it));
         const ReqDesc &d = R[r];
-        const long long local = it - pst[r];
+        const long long local = it - first_item(pst, n_req, r);
         const int A = d.fd_A, b = (int)(local / A), n1 = (int)(local % A);
         const long long M = (long long)A * kCodeLen, L = (long long)d.Tc * d.N;
         const long long base = (long long)(d.b0 + b) * L;
@@ -2037,7 +2045,7 @@ __global__ __launch_bounds__(256) void k_fd_pass2(const ReqDesc *__restrict__ R,
     for (long long it = blockIdx.x; it < total; it += gridDim.x) {
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
-        const long long local = it - pst[r];
+        const long long local = it - first_item(pst, n_req, r);
         const int A = d.fd_A, PTc = d.fd_PTc;
         const int b = (int)(local / kChunks), sig0 = (int)(local % kChunks) * kFdCols;
         const int ncol = min(kFdCols, kCodeLen - sig0);
@@ -2166,7 +2174,7 @@ __global__ __launch_bounds__(kSynthThreads) void k_fd_synth(const ReqDesc *__res
         if (it < 0) break;
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
-        const int kb = (int)(it - pst[r]);
+        const int kb = (int)(it - first_item(pst, n_req, r));
         const int k = kb / d.Nnc, b = kb - k * d.Nnc;
         const int N = d.N, spc = d.spc, A = d.fd_A, PTc = d.fd_PTc;
         const long long M = (long long)A * kCodeLen;
@@ -2479,7 +2487,7 @@ __global__ __launch_bounds__(kGenThreads) void k_gen_spec(const ReqDesc *__restr
         if (d.gen_P != P || d.gen_rows) continue;
         const int N = d.N, M = d.gen_M;
         const int S = d.gen_seg ? 2 : 1, seg = d.gen_seg ? gen_segment(N) : N;
-        const long long local = it - pst[r];
+        const long long local = it - first_item(pst, n_req, r);
         const long long idx = local / S;
         const int h = (int)(local - idx * S), n0 = h * seg;
         float2 *dst;
@@ -2612,7 +2620,7 @@ __global__ __launch_bounds__(kGenThreads) void k_gen_corr(const ReqDesc *__restr
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
         if (d.gen_P != P || d.gen_rows) continue;
-        const long long local = it - pst[r];
+        const long long local = it - first_item(pst, n_req, r);
         const int k = (int)(local / d.n_prn), pi = (int)(local % d.n_prn);
         gen_corr_item<P>(d, k, pi, tw, gen, x, s_tw);
     }
@@ -2906,7 +2914,7 @@ __global__ __launch_bounds__(RowFft<P>::T) void k_gen_spec_rows(const ReqDesc *_
         if (d.gen_P != P || !d.gen_rows) continue;
         const int N = d.N, M = d.gen_M;
         const int S = d.gen_seg ? 2 : 1, seg = d.gen_seg ? gen_segment(N) : N;
-        const long long local = it - pst[r];
+        const long long local = it - first_item(pst, n_req, r);
         const long long idx = local / S;
         const int h = (int)(local - idx * S), n0 = h * seg;
         const bool halves = P == kGenLds && !d.gen_seg && M > P;
@@ -3003,7 +3011,7 @@ __global__ __launch_bounds__(RowFft<P>::T *RowFft<P>::kGroups)
         const ReqDesc &d = R[r];
         const int N = d.N, M = d.gen_M;
         if (d.gen_P != P || !d.gen_rows || MODE != (M == P ? 1 : d.gen_seg ? 2 : 0)) continue;
-        const long long local = it - pst[r];
+        const long long local = it - first_item(pst, n_req, r);
         const int n_grp = (d.n_prn + F::kGroups - 1) / F::kGroups;
         const int k = (int)(local / n_grp);
         // the transform's threads t and PRN; a PRN past the list's end repeats the last one, unwritten
@@ -3138,6 +3146,15 @@ __global__ __launch_bounds__(RowFft<P>::T *RowFft<P>::kGroups)
 // ===========================================================================
 // detection: column max over Doppler, argmax, second peak, mean; refinement
 // ===========================================================================
+// Sum over the first wave's lanes in a fixed binary tree (32 + 32, 16 + 16, ...);
+// lane 0 has it.
+__device__ __forceinline__ float wave_tree_sum(float v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
+    return v;
+}
+
 // Work item = (request, PRN, block of 256 lags).  Q[tau] = max_k P (lowest k
 // on ties), K = that k; part = the block's FP32 sum of P: each column summed
 // in row order, then the block's columns in a fixed binary tree, so the mean
@@ -3154,7 +3171,7 @@ __global__ __launch_bounds__(kPeakThreads) void k_colmax(const ReqDesc *__restri
     for (long long it = blockIdx.x; it < total; it += gridDim.x) {
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
-        const long long local = it - pst[r];
+        const long long local = it - first_item(pst, n_req, r);
         const int p = (int)(local / d.n_tau_blk), blk = (int)(local % d.n_tau_blk);
         const int N = d.N, tau = blk * kPeakThreads + threadIdx.x;
         float colsum = 0.f;
@@ -3192,99 +3209,15 @@ __global__ __launch_bounds__(kPeakThreads) void k_colmax(const ReqDesc *__restri
         __syncthreads();
         red[threadIdx.x] = colsum;
         __syncthreads();
-        for (int st = kPeakThreads / 2; st > 0; st >>= 1) {
+        // the tree's upper levels in LDS, the last six in the first wave
+        for (int st = kPeakThreads / 2; st >= 64; st >>= 1) {
             if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
             __syncthreads();
         }
-        if (threadIdx.x == 0) part[d.part_off + (long long)p * d.n_tau_blk + blk] = red[0];
-    }
-}
-
-// Work item = (request, PRN): argmax (lowest tau on ties), second peak outside
-// +-spc (circular), mean, ratio test.
-__global__ __launch_bounds__(kArgThreads) void k_peak(const ReqDesc *__restrict__ R, BatchHdr *H,
-                                                       const long long *pre, const float *Q,
-                                                       const int32_t *K, const float *part)
-{
-    __shared__ float sv[kArgThreads];
-    __shared__ int st[kArgThreads];
-    const int tid = threadIdx.x;
-    const int n_req = H->n_req;
-    const long long total = H->total[kStPeak];
-    const long long *pst = pre + (long long)kStPeak * (n_req + 1);
-    for (long long it = blockIdx.x; it < total; it += gridDim.x) {
-        const int r = find_req(pst, n_req, it);
-        const ReqDesc &d = R[r];
-        const int p = (int)(it - pst[r]);
-        const int N = d.N;
-        const float *q = Q + d.qk_off + (long long)p * N;
-        float bv = -INFINITY;
-        int bt = 0x7fffffff;
-        for (int tau = tid; tau < N; tau += kArgThreads) {
-            float v = q[tau];
-            if (v > bv) {
-                bv = v;
-                bt = tau;
-            }
+        if (threadIdx.x < 64) {
+            const float v = wave_tree_sum(red[threadIdx.x]);
+            if (threadIdx.x == 0) part[d.part_off + (long long)p * d.n_tau_blk + blk] = v;
         }
-        __syncthreads();
-        sv[tid] = bv;
-        st[tid] = bt;
-        __syncthreads();
-        for (int s = kArgThreads / 2; s > 0; s >>= 1) {
-            if (tid < s) {
-                float v2 = sv[tid + s];
-                int t2 = st[tid + s];
-                if (v2 > sv[tid] || (v2 == sv[tid] && t2 < st[tid])) {
-                    sv[tid] = v2;
-                    st[tid] = t2;
-                }
-            }
-            __syncthreads();
-        }
-        const float peak = sv[0];
-        // a grid with no ordered maximum (all NaN) leaves tau* unset: keep it in range
-        const int tstar = (st[0] >= 0 && st[0] < N) ? st[0] : 0;
-        __syncthreads();
-        float m2 = -INFINITY;
-        for (int tau = tid; tau < N; tau += kArgThreads) {
-            int dd = abs(tau - tstar);
-            dd = min(dd, N - dd);
-            if (dd > d.spc) m2 = fmaxf(m2, q[tau]);
-        }
-        sv[tid] = m2;
-        __syncthreads();
-        for (int s = kArgThreads / 2; s > 0; s >>= 1) {
-            if (tid < s) sv[tid] = fmaxf(sv[tid], sv[tid + s]);
-            __syncthreads();
-        }
-        const float second = sv[0] == -INFINITY ? 0.f : sv[0];
-        __syncthreads();
-        // the blocks' partial sums in a fixed binary tree (FP32)
-        float ps = 0.f;
-        for (int i = tid; i < d.n_tau_blk; i += kArgThreads) ps += part[d.part_off + (long long)p * d.n_tau_blk + i];
-        sv[tid] = ps;
-        __syncthreads();
-        for (int s = kArgThreads / 2; s > 0; s >>= 1) {
-            if (tid < s) sv[tid] += sv[tid + s];
-            __syncthreads();
-        }
-        if (tid == 0) {
-            const float sum = sv[0];
-            gnss_peak rr;
-            rr.prn = d.prns[p];
-            rr.doppler_bin = K[d.qk_off + (long long)p * N + tstar];
-            rr.code_phase = tstar;
-            rr.peak = peak;
-            rr.second = second;
-            rr.mean = sum / ((float)d.n_dopp * (float)N);
-            rr.ratio = second > 0.f ? peak / second : INFINITY;
-            rr.detected = rr.ratio >= d.threshold ? 1 : 0;
-            rr.doppler_hz = 0.0;
-            rr.code_phase_frac = (double)tstar;
-            d.peaks[p] = rr;
-        }
-        __syncthreads();
     }
 }
 
@@ -3295,33 +3228,136 @@ __device__ __forceinline__ double parabola(double ym, double y0, double yp)
     return 0.5 * (ym - yp) / den;
 }
 
-// FP64 sub-bin refinement, one thread per (request, PRN): the only FP64
-// arithmetic of a search on the device (the carrier and code-Doppler steps
-// are computed on the host; FP64 elsewhere in this file builds the constant
-// tables once per context: the carrier LUT, twiddles and exact-length code
-// spectra).
-__global__ void k_interp(const ReqDesc *__restrict__ R, BatchHdr *H, const long long *pre)
+// Work item = (request, PRN): argmax (lowest tau on ties), second peak outside
+// +-spc (circular), mean, ratio test, and the FP64 sub-bin refinement (the only
+// FP64 arithmetic of a search on the device: the carrier and code-Doppler
+// steps are computed on the host; FP64 elsewhere in this file builds the
+// constant tables once per context: the carrier LUT, twiddles and exact-length
+// code spectra).  Latency is what it costs: each thread keeps its column
+// maxima in registers (up to kPeakLags lags, read once, all loads in flight;
+// a longer grid of the caller's is read twice) and the reductions are wave
+// shuffles and one exchange in LDS, three barriers in all; with LDS trees,
+// forty barriers and the refinement as a launch of its own a strong-signal
+// search (32 PRNs, 21 bins, 4092 lags) spent 11.1 us here and spends 7.0.
+__global__ __launch_bounds__(kArgThreads) void k_peak(const ReqDesc *__restrict__ R, BatchHdr *H,
+                                                       const long long *pre, const float *Q,
+                                                       const int32_t *K, const float *part)
 {
+    constexpr int kWaves = kArgThreads / 64, kPer = kPeakLags / kArgThreads;
+    __shared__ float sv[kWaves], sm[kWaves], su[kWaves];
+    __shared__ int st[kWaves];
+    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const int n_req = H->n_req;
     const long long total = H->total[kStPeak];
     const long long *pst = pre + (long long)kStPeak * (n_req + 1);
-    for (long long it = (long long)blockIdx.x * blockDim.x + threadIdx.x; it < total;
-         it += (long long)gridDim.x * blockDim.x) {
+    for (long long it = blockIdx.x; it < total; it += gridDim.x) {
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
-        const int p = (int)(it - pst[r]);
-        gnss_peak *pk = d.peaks + p;
-        gnss_peak rr = *pk;
-        const int N = d.N, nd = d.n_dopp;
-        const GNSS_GLOBAL float *Gp = gmem(d.grid) + (long long)p * nd * N;
-        const int k = rr.doppler_bin, t = rr.code_phase;
-        double y0 = Gp[(long long)k * N + t];
-        double dc = parabola(Gp[(long long)k * N + (t - 1 + N) % N], y0, Gp[(long long)k * N + (t + 1) % N]);
-        double dd = 0.0;
-        if (k > 0 && k < nd - 1) dd = parabola(Gp[(long long)(k - 1) * N + t], y0, Gp[(long long)(k + 1) * N + t]);
-        double fk = __dadd_rn(d.lo, __dmul_rn((double)k, d.step));
-        pk->doppler_hz = __dadd_rn(fk, __dmul_rn(dd, d.step));
-        pk->code_phase_frac = __dadd_rn((double)t, dc);
+        const int p = (int)(it - first_item(pst, n_req, r));
+        const int N = d.N;
+        const float *q = Q + d.qk_off + (long long)p * N;
+        // the blocks' partial sums in a fixed binary tree (FP32)
+        float ps = 0.f;
+        for (int i = tid; i < d.n_tau_blk; i += kArgThreads) ps += part[d.part_off + (long long)p * d.n_tau_blk + i];
+        ps = wave_tree_sum(ps);
+        float v[kPer];
+        auto load = [&](unsigned t0) {
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) v[j] = t0 + j * kArgThreads < (unsigned)N ? q[t0 + j * kArgThreads] : -INFINITY;
+        };
+        float bv = -INFINITY;
+        int bt = 0x7fffffff;
+        for (unsigned t0 = tid; t0 < (unsigned)N; t0 += kPeakLags) {
+            load(t0);
+#pragma unroll
+            for (int j = 0; j < kPer; ++j)
+                if (v[j] > bv) {
+                    bv = v[j];
+                    bt = (int)t0 + j * kArgThreads;
+                }
+        }
+        // the row of this thread's own maximum: used if it is the overall one
+        const int own = bt;
+        const int kown = K[d.qk_off + (long long)p * N + (own < N ? own : 0)];
+        auto better = [&](float v2, int t2) {
+            if (v2 > bv || (v2 == bv && t2 < bt)) {
+                bv = v2;
+                bt = t2;
+            }
+        };
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const float v2 = __shfl_xor(bv, o);
+            const int t2 = __shfl_xor(bt, o);
+            better(v2, t2);
+        }
+        __syncthreads();  // the previous item's reads of the exchange are done
+        if (l == 0) {
+            sv[w] = bv;
+            st[w] = bt;
+        }
+        __syncthreads();
+        for (int i = 0; i < kWaves; ++i) better(sv[i], st[i]);
+        // a grid with no ordered maximum (all NaN) leaves tau* unset: keep it in range
+        const int tstar = (bt >= 0 && bt < N) ? bt : 0;
+        // The refinement's samples are loaded by the thread that found the maximum,
+        // behind the search for the second peak: parabolas along tau (circular) and
+        // along Doppler (not at the ends).
+        const bool owner = own == tstar || (bt != tstar && tid == 0);
+        const int nd = d.n_dopp, k = kown;
+        const bool inner = k > 0 && k < nd - 1;
+        float y0 = 0.f, tm = 0.f, tp = 0.f, km = 0.f, kp = 0.f;
+        if (owner) {
+            const GNSS_GLOBAL float *row = gmem(d.grid) + ((long long)p * nd + k) * N;
+            y0 = row[tstar];
+            tm = row[tstar ? tstar - 1 : N - 1];
+            tp = row[tstar + 1 < N ? tstar + 1 : 0];
+            km = row[tstar - (inner ? (long long)N : 0)];
+            kp = row[tstar + (inner ? (long long)N : 0)];
+        }
+        float m2 = -INFINITY;
+        for (unsigned t0 = tid; t0 < (unsigned)N; t0 += kPeakLags) {
+            if (N > kPeakLags) load(t0);
+#pragma unroll
+            for (int j = 0; j < kPer; ++j) {
+                int dd = abs((int)t0 + j * kArgThreads - tstar);
+                dd = min(dd, N - dd);
+                if (dd > d.spc) m2 = fmaxf(m2, v[j]);  // past the last lag: -infinity
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) m2 = fmaxf(m2, __shfl_xor(m2, o));
+        if (l == 0) {
+            sm[w] = m2;
+            su[w] = ps;
+        }
+        __syncthreads();
+        if (owner) {
+#pragma unroll
+            for (int i = 0; i < kWaves; ++i) m2 = fmaxf(m2, sm[i]);
+            float us[kWaves];
+#pragma unroll
+            for (int i = 0; i < kWaves; ++i) us[i] = su[i];
+#pragma unroll
+            for (int o = kWaves / 2; o > 0; o >>= 1)
+#pragma unroll
+                for (int i = 0; i < o; ++i) us[i] += us[i + o];
+            const float second = m2 == -INFINITY ? 0.f : m2;
+            const double dc = parabola(tm, y0, tp), dd = inner ? parabola(km, y0, kp) : 0.0;
+            const double fk = __dadd_rn(d.lo, __dmul_rn((double)k, d.step));
+            gnss_peak rr;
+            rr.prn = d.prns[p];
+            rr.doppler_bin = k;
+            rr.code_phase = tstar;
+            rr.peak = bv;
+            rr.second = second;
+            rr.mean = us[0] / ((float)nd * (float)N);
+            rr.ratio = second > 0.f ? bv / second : INFINITY;
+            rr.detected = rr.ratio >= d.threshold ? 1 : 0;
+            rr.doppler_hz = __dadd_rn(fk, __dmul_rn(dd, d.step));
+            rr.code_phase_frac = __dadd_rn((double)tstar, dc);
+            d.peaks[p] = rr;
+        }
     }
 }
 
@@ -3584,10 +3620,6 @@ hipError_t launch_batch(const Launch &L, const Tables &T, int2 *d_F, void *d_G, 
         hipLaunchKernelGGL(k_peak, dim3(grid_for(L.total[kStPeak], 4LL * n_cu, false)), dim3(kArgThreads), 0,
                            s, L.reqs, L.hdr, L.pre, d_Q, d_K, d_part);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        const long long ni = (L.total[kStPeak] + 63) / 64;
-        hipLaunchKernelGGL(k_interp, dim3((unsigned)(ni < 1 ? 1 : ni > 65536 ? 65536 : ni)), dim3(64), 0, s,
-                           L.reqs, L.hdr, L.pre);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return mark(4);
 }
@@ -3749,7 +3781,7 @@ __global__ __launch_bounds__(kTrackThreads) void k_track(const TrackDesc *__rest
         const int r = find_req(pre, n_req, it);
         const TrackDesc &d = R[r];
         const int groups = (d.n_ch + kTrackCG - 1) / kTrackCG;
-        const long long local = it - pre[r];
+        const long long local = it - first_item(pre, n_req, r);
         const int e = (int)(local / groups), c0 = (int)(local - (long long)e * groups) * kTrackCG;
         const long long n_e = d.start + (long long)e * d.epoch_len;  // the epoch's first sample
         __syncthreads();  // table staged; previous item done with s_sign and s_red

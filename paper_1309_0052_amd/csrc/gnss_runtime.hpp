@@ -37,6 +37,11 @@ struct DevBuf {
     bool owned = true;  // false: a view into another allocation (never freed on its own)
 };
 
+// The events that say when a workspace's buffers are idle order nothing but the
+// freeing of those buffers: no host read and no other device waits on them, so
+// they need no write-back of the caches to the host.
+constexpr unsigned kUseEventFlags = hipEventDisableTiming | hipEventDisableSystemFence;
+
 // Device buffers of one in-flight batch and the pinned staging of its
 // metadata.
 struct Workspace {
