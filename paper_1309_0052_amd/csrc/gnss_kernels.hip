@@ -1413,6 +1413,7 @@ __global__ __launch_bounds__(64 * kCorrWavesH) __attribute__((amdgpu_waves_per_e
 __device__ double pfa_weight(int L, bool inv, int i_in, int p_in, int i_out, int p_out)
 {
     if (i_in < 0 || i_out < 0 || i_in >= L || i_out >= L) return 0.0;
+    if (L == pfa::kN2) (inv ? i_in : i_out) = pfa::column_b(inv ? i_in : i_out);
     const int e = (i_in * i_out) % L;
     double sn, cs;
     sincospi(2.0 * (double)e / (double)L, &sn, &cs);
@@ -1604,9 +1605,9 @@ __device__ __forceinline__ void fft_x_vector(const int2 *xs, const pfa::FwdB &B,
         }
     pfa::f4 o[2][6];
     pfa::forward(a1, B, o);
-    if (l == 0) {  // bin 0 (a = 0, b = 0): the vector's sum
-        o[0][0].x = Sr * f;
-        o[0][1].x = Si * f;
+    if (l == 0) {  // bin 0 (a = 0, b = 0, column 32): the vector's sum
+        o[0][4].x = Sr * f;
+        o[0][5].x = Si * f;
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -1654,15 +1655,20 @@ __global__ __launch_bounds__(256) void k_fft_x(const int2 *F, const pfa::u4 *__r
 // LDS copy of one stored spectrum: the four full fragments (1 KB each) and
 // the 128-byte tail, staged as 32 dwords (lanes 32..63 repeat them).
 constexpr int kXBuf = pfa::kTailUnit + 16;  // u4 units per LDS spectrum buffer
+template <bool TAIL>
 __device__ __forceinline__ void stage_spectrum(const pfa::u4 *src, pfa::u4 *dst, int l)
 {
     typedef __attribute__((address_space(1))) const void gvoid;
     typedef __attribute__((address_space(3))) void lvoid;
-#pragma unroll
-    for (int f = 0; f < 4; ++f)
-        __builtin_amdgcn_global_load_lds((gvoid *)(src + f * 64 + l), (lvoid *)(dst + f * 64), 16, 0, 0);
-    const uint32_t *tail = (const uint32_t *)(src + pfa::kTailUnit);
-    __builtin_amdgcn_global_load_lds((gvoid *)(tail + (l & 31)), (lvoid *)(dst + pfa::kTailUnit), 4, 0, 0);
+    // (the immediate offset moves both the global and the LDS address)
+    __builtin_amdgcn_global_load_lds((gvoid *)(src + l), (lvoid *)dst, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((gvoid *)(src + l), (lvoid *)dst, 16, 1024, 0);
+    __builtin_amdgcn_global_load_lds((gvoid *)(src + l), (lvoid *)dst, 16, 2048, 0);
+    __builtin_amdgcn_global_load_lds((gvoid *)(src + l), (lvoid *)dst, 16, 3072, 0);
+    if constexpr (TAIL) {
+        const uint32_t *tail = (const uint32_t *)(src + pfa::kTailUnit);
+        __builtin_amdgcn_global_load_lds((gvoid *)(tail + (l & 31)), (lvoid *)(dst + pfa::kTailUnit), 4, 0, 0);
+    }
 }
 
 // Value of lane 4 q + 1 in lane 4 q (DPP quad permutation [1, 1, 3, 3]).
@@ -1682,6 +1688,154 @@ __device__ __forceinline__ pfa::u4 cmul_conj_frag(pfa::u4 g, pfa::u4 c)
     return pfa::u4{h2_bits(yr0), h2_bits(yr1), h2_bits(yi0), h2_bits(yi1)};
 }
 
+// The 33rd column's 31-point transforms of 16 (block, PRN) pairs in LDS: rows of
+// [part][n1 < 32] floats, padded against bank conflicts of the lanes' writes.
+constexpr int kCol0Row = 68;
+static_assert(kCorrWavesX * 16 * kCol0Row <= 1024 * (kCorrWavesX + 1), "held in the grid's staging area");
+
+// Sum over an item's blocks of |IDFT(G conj(C))|^2 for NP PRNs (one or two), by
+// one wave.  Block b + 1's spectrum is copied into the wave's other LDS buffer
+// (direct-to-LDS loads, no registers) while block b is transformed.  Matrix and
+// vector instructions take turns on a SIMD, so their sum is what it costs; the
+// 33rd column (b = 0) fits no tile and is kept from costing tiles of its own:
+// * its 31-point transforms are made for 16 (block, PRN) pairs at once, as the
+//   16 columns of one product with the weights as A operand, rounded to FP16 as
+//   every other column is and kept in LDS for the blocks that follow;
+// * its weight in the 33-pass is 1 for every output, so it enters that pass as
+//   the accumulator's first value (the same for all columns of a row).
+// 36.5 matrix instructions per transform instead of 54 (8 + 10 went to that column).
+// With those gone the waves waited for their spectra, so a wave takes two PRNs per
+// staged spectrum and nothing between one copy and the next waits for memory.  The
+// weak-signal search's correlations (32 PRNs, 121 bins, 25 blocks, 16 phases):
+// 1.11 -> 0.87 ms, with matrix (54%) and vector instructions (46%) back to back.
+template <int NP>
+__device__ __forceinline__ void blocks_x(float (&acc)[NP][2][3][4], const ReqDesc &d, const pfa::u4 *gx, const int *ex,
+                                         const pfa::u4 *__restrict__ s_c, pfa::u4 *__restrict__ bufs,
+                                         float *__restrict__ col0, const pfa::InvB &B, int l)
+{
+    constexpr int NB = 16 / NP;   // blocks per batch of the 33rd column
+    constexpr int kRow = kCol0Row;
+    const int g = l >> 4, c = l & 15;
+    const long long step = (long long)d.spc * pfa::kUnits;
+    const int Nnc = d.Nnc, spc = d.spc;
+    const pfa::f4 z = {0.f, 0.f, 0.f, 0.f};
+    stage_spectrum<false>(gx, bufs, l);
+    int ev = 0, e_ref = ex[0], e_max = e_ref;
+    for (int b = 0; b < Nnc; ++b) {
+        const int beta = b & (NB - 1);
+        if (beta == 0) {
+            const int bc = min(b + (c & (NB - 1)), Nnc - 1);
+            const pfa::u4 *tp = gx + (long long)bc * step + pfa::kTailUnit + g;
+            const pfa::u4 *cp = s_c + (NP == 1 ? 0 : (c >> 3) * pfa::kUnits) + pfa::kTailUnit + g;
+            const pfa::u4 t0 = tp[0], t1 = tp[4];
+            ev = ex[(long long)bc * spc];
+            const pfa::u4 y0 = cmul_conj_frag(t0, cp[0]), y1 = cmul_conj_frag(t1, cp[4]);
+            wave_lds_order();  // the previous batch's reads come before these writes
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+                const pfa::f4 v = pfa::mma32(B.b31[1][n], y1, pfa::mma32(B.b31[0][n], y0, z));
+                float4 r;
+                r.x = (float)(_Float16)v.x;
+                r.y = (float)(_Float16)v.y;
+                r.z = (float)(_Float16)v.z;
+                r.w = (float)(_Float16)v.w;
+                *(float4 *)(col0 + c * kRow + 32 * (n >> 1) + 16 * (n & 1) + 4 * g) = r;
+            }
+            wave_lds_order();
+            asm volatile("" : "+v"(ev));  // arrived here: no wait for it behind the next block's copy
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // block b is in LDS
+        const pfa::u4 *cur = bufs + (b & 1) * kXBuf;
+        pfa::u4 gf[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) gf[i] = cur[i * 64 + l];
+        // The other buffer was last read for block b - 1.  (The copy is issued behind
+        // this block's reads, and the other LDS arrays are declared disjoint from the
+        // buffers: the compiler waits for a copy in flight before any LDS read that
+        // might see it.)
+        if (b + 1 < Nnc)
+            stage_spectrum<false>((const pfa::u4 *)uniform64((long long)(gx + (b + 1) * step)),
+                                  bufs + ((b + 1) & 1) * kXBuf, l);
+        // The sums are kept in units of 2^(2 e_ref), e_ref the exponent of the last
+        // block added: a block at e_ref adds its power unscaled.
+        const int e_cur = __builtin_amdgcn_readlane(ev, beta);
+        bool drop = false;
+        if (e_cur != e_ref) {
+            // Another block exponent: bring the sums to it (a power of two, exact).
+            // A block's power is below 2^30 in its own units and Nnc < 2^17, so the
+            // sums stay below 2^47 in the units of the largest exponent so far,
+            // e_max; scaling to e_cur >= e_max - 30 multiplies them by at most 2^60
+            // over that, which stays finite.  A block more than 2^30 below e_max
+            // adds less than 2^-60 of that block's power and is dropped (an
+            // all-zero block has exponent 0 and power 0).
+            drop = e_cur < e_max - 30;
+        }
+        if (e_cur != e_ref && !drop) {
+            const float f = ldexpf(1.f, 2 * (e_ref - e_cur));
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int h = 0; h < 3; ++h)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[p][u][h][q] *= f;
+            e_ref = e_cur;
+            e_max = max(e_max, e_cur);
+        }
+        if (drop) continue;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            pfa::u4 a1[2][2], a2[2][2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int ss = 0; ss < 2; ++ss)
+                    a1[t][ss] = cmul_conj_frag(gf[2 * t + ss], s_c[p * pfa::kUnits + (2 * t + ss) * 64 + l]);
+            const float *z0 = col0 + (beta + NB * p) * kRow + 4 * g;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                pfa::f4 d1[4];
+#pragma unroll
+                for (int n = 0; n < 4; ++n) d1[n] = pfa::mma32(a1[t][1], B.b31[1][n], pfa::mma32(a1[t][0], B.b31[0][n], z));
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    a2[u][t] = pfa::u4{pfa::pack2(d1[u].x, d1[u].y), pfa::pack2(d1[u].z, d1[u].w),
+                                       pfa::pack2(d1[u + 2].x, d1[u + 2].y), pfa::pack2(d1[u + 2].z, d1[u + 2].w)};
+            }
+            // |.|^2 into the sums.  Output column 32 has its real part in lane c = 0 and
+            // its imaginary part in lane c = 1: each lane sums its own square and the
+            // two are added at the end.
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const pfa::f4 c_re = *(const pfa::f4 *)(z0 + 16 * u), c_im = *(const pfa::f4 *)(z0 + 32 + 16 * u);
+                const pfa::f4 c_32 = *(const pfa::f4 *)(z0 + 32 * (c & 1) + 16 * u);
+#pragma unroll
+                for (int v = 0; v < 5; ++v) {
+                    const pfa::f4 o = pfa::mma32(a2[u][1], B.b33[1][v],
+                                                 pfa::mma32(a2[u][0], B.b33[0][v], v == 4 ? c_32 : v & 1 ? c_im : c_re));
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc[p][u][v >> 1][q] = fmaf(o[q], o[q], acc[p][u][v >> 1][q]);
+                }
+            }
+        }
+    }
+    // column 32: lane c = 0 adds lane c = 1's imaginary part; then the sums in
+    // absolute units
+    const float f = ldexpf(1.f, 2 * e_ref);
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[p][u][2][q] += from_next_lane(acc[p][u][2][q]);
+#pragma unroll
+            for (int h = 0; h < 3; ++h)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[p][u][h][q] *= f;
+        }
+}
+
 // Correlation, exact-length mode.  Work item = (request, PRN tile, chunk of
 // kCorrWavesX (Doppler, phase) items); one wave per item; the tile's PRNs in
 // turn, each over all blocks with its sums in registers, then written.
@@ -1693,7 +1847,8 @@ __global__ __launch_bounds__(64 * kCorrWavesX) void k_corr_x(const ReqDesc *__re
 {
     constexpr int W = kCorrWavesX;
     constexpr int kPad = W + 1;
-    __shared__ pfa::u4 s_c[pfa::kUnits];
+    constexpr int NP = PAIRS ? 1 : 2;  // PRNs a wave works on at a time
+    __shared__ pfa::u4 s_c[NP * pfa::kUnits];
     __shared__ float s_stage[1024 * kPad];
     __shared__ pfa::u4 s_g[W * 2 * kXBuf];  // two block spectra per wave
     __shared__ long long s_item;
@@ -1720,54 +1875,27 @@ __global__ __launch_bounds__(64 * kCorrWavesX) void k_corr_x(const ReqDesc *__re
         const int spc = d.spc;
         const int k = item / spc, s = item - k * spc;
         const long long v0 = d.vec_off + (long long)k * d.Nnc * spc + s;
-        for (int pp = 0; pp < pt; ++pp) {
+        for (int pp = 0; pp < pt; pp += NP) {
             const int pi = ptile * pt + pp;
             if (pi >= d.n_prn) break;
-            __syncthreads();  // the previous PRN's reads of s_c and s_stage are done
-            for (int i = tid; i < pfa::kUnits; i += 64 * W) s_c[i] = CSx[(long long)d.prns[pi] * pfa::kUnits + i];
+            const int np = min(NP, min(pt - pp, d.n_prn - pi));
+            __syncthreads();  // the previous PRNs' reads of s_c and s_stage are done
+            for (int p = 0; p < np; ++p)
+                for (int i = tid; i < pfa::kUnits; i += 64 * W)
+                    s_c[p * pfa::kUnits + i] = CSx[(long long)d.prns[pi + p] * pfa::kUnits + i];
             __syncthreads();
-            float acc[2][3][4];
+            float acc[NP][2][3][4];
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
+            for (int p = 0; p < NP; ++p)
 #pragma unroll
-                for (int h = 0; h < 3; ++h)
+                for (int u = 0; u < 2; ++u)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) acc[u][h][q] = 0.f;
+                    for (int h = 0; h < 3; ++h)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[p][u][h][q] = 0.f;
             if (active) {
-                // Block b + 1's spectrum is copied from HBM into the wave's other
-                // LDS buffer (direct-to-LDS loads, no registers) while block b's
-                // transform runs.
                 pfa::u4 *bufs = s_g + w * 2 * kXBuf;
                 auto spectrum = [&](int b) { return Gx + (v0 + (long long)b * spc) * pfa::kUnits; };
-                auto product = [&](const pfa::u4 *cur, pfa::u4 (&a1)[3][2]) {
-#pragma unroll
-                    for (int t = 0; t < 3; ++t)
-#pragma unroll
-                        for (int ss = 0; ss < 2; ++ss) {
-                            const int unit = t < 2 ? (2 * t + ss) * 64 + l : pfa::kTailUnit + 4 * ss + g;
-                            const bool has = t < 2 || c == 0;
-                            a1[t][ss] = has ? cmul_conj_frag(cur[unit], s_c[unit]) : zero4;
-                        }
-                };
-                // |.|^2 into the sums, which are kept in units of 2^(2 e_ref), e_ref
-                // the exponent of the last block added: a block at e_ref adds its
-                // power unscaled.  Column 32 has its real part in lane c = 0 and its
-                // imaginary part in lane c = 1: each lane sums its own square and
-                // the two are added at the end.
-                auto power_unit = [&](const pfa::f4 (&o)[2][5]) {
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-#pragma unroll
-                        for (int h = 0; h < 2; ++h)
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                const float yr = o[u][2 * h][q], yi = o[u][2 * h + 1][q];
-                                acc[u][h][q] = fmaf(yi, yi, fmaf(yr, yr, acc[u][h][q]));
-                            }
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) acc[u][2][q] = fmaf(o[u][4][q], o[u][4][q], acc[u][2][q]);
-                    }
-                };
                 if constexpr (PAIRS) {
                     // Navigation-bit hypotheses: blocks 2i and 2i + 1 combined
                     // coherently with both relative signs, max over the two;
@@ -1776,8 +1904,8 @@ __global__ __launch_bounds__(64 * kCorrWavesX) void k_corr_x(const ReqDesc *__re
                     // which is free until the item's grid write.
                     float *pplus = s_stage + w * 1024;
                     for (int b = 0; b < d.Nnc; b += 2) {
-                        stage_spectrum(spectrum(b), bufs, l);
-                        stage_spectrum(spectrum(b + 1), bufs + kXBuf, l);
+                        stage_spectrum<true>(spectrum(b), bufs, l);
+                        stage_spectrum<true>(spectrum(b + 1), bufs + kXBuf, l);
                         const int ea = E[v0 + (long long)b * spc], eb = E[v0 + (long long)(b + 1) * spc];
                         const int e = max(ea, eb);
                         // 2^(ea - e) and 2^(eb - e) in FP16 (exact; below 2^-24 they vanish,
@@ -1829,86 +1957,43 @@ __global__ __launch_bounds__(64 * kCorrWavesX) void k_corr_x(const ReqDesc *__re
                                             if (hyp == 0)
                                                 *slot = pw;
                                             else
-                                                acc[u][h][q] = fmaf(fmaxf(*slot, pw), sc, acc[u][h][q]);
+                                                acc[0][u][h][q] = fmaf(fmaxf(*slot, pw), sc, acc[0][u][h][q]);
                                         }
                                     }
                             lds_fence();
                         }
                     }
                 } else {
-                stage_spectrum(spectrum(0), bufs, l);
-                int e_cur = E[v0], e_ref = e_cur, e_max = e_cur;
-                for (int b = 0; b < d.Nnc; ++b) {
-                    pfa::u4 a1[3][2];
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // block b is in LDS
-                    product(bufs + (b & 1) * kXBuf, a1);
-                    int e_next = 0;
-                    if (b + 1 < d.Nnc) {
-                        // the other buffer was last read by block b - 1's product
-                        stage_spectrum(spectrum(b + 1), bufs + ((b + 1) & 1) * kXBuf, l);
-                        e_next = E[v0 + (long long)(b + 1) * spc];
+                    float *col0 = s_stage + w * 16 * kCol0Row;
+                    if (np == NP) {
+                        blocks_x<NP>(acc, d, Gx + v0 * pfa::kUnits, E + v0, s_c, bufs, col0, B, l);
+                    } else {  // a tile's last PRN
+                        float(&a1)[1][2][3][4] = *(float(*)[1][2][3][4]) & acc[0];
+                        blocks_x<1>(a1, d, Gx + v0 * pfa::kUnits, E + v0, s_c, bufs, col0, B, l);
                     }
-                    pfa::f4 o[2][5];
-                    pfa::inverse(a1, B, o);
-                    if (e_cur != e_ref) {
-                        // Another block exponent: bring the sums to it (a power of
-                        // two, exact).  A block's power is below 2^30 in its own
-                        // units and Nnc < 2^17, so the sums stay below 2^47 in the
-                        // units of the largest exponent so far, e_max; scaling to
-                        // e_cur >= e_max - 30 multiplies them by at most 2^60 over
-                        // that, which stays finite.  A block more than 2^30 below
-                        // e_max adds less than 2^-60 of that block's power and is
-                        // dropped (an all-zero block has exponent 0 and power 0).
-                        if (e_cur >= e_max - 30) {
-                            const float f = ldexpf(1.f, 2 * (e_ref - e_cur));
-#pragma unroll
-                            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                                for (int h = 0; h < 3; ++h)
-#pragma unroll
-                                    for (int q = 0; q < 4; ++q) acc[u][h][q] *= f;
-                            e_ref = e_cur;
-                            e_max = max(e_max, e_cur);
-                        } else {
-#pragma unroll
-                            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                                for (int v = 0; v < 5; ++v) o[u][v] = pfa::f4{0.f, 0.f, 0.f, 0.f};
-                        }
-                    }
-                    power_unit(o);
-                    e_cur = e_next;
-                }
-                // column 32: lane c = 0 adds lane c = 1's imaginary part; then
-                // the sums in absolute units
-                const float f = ldexpf(1.f, 2 * e_ref);
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) acc[u][2][q] += from_next_lane(acc[u][2][q]);
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int h = 0; h < 3; ++h)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) acc[u][h][q] *= f;
                 }
             }
-            __syncthreads();  // every wave is done with s_stage (the pair hypotheses use it)
-            if (active) {
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
+            for (int p = 0; p < NP; ++p) {
+                if (p >= np) break;
+                // every wave is done with s_stage (the 33rd column, the pair hypotheses
+                // and the previous PRN's write use it)
+                __syncthreads();
+                if (active) {
 #pragma unroll
-                    for (int h = 0; h < 3; ++h)
+                    for (int u = 0; u < 2; ++u)
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int n1 = 16 * u + 4 * g + q, n2 = 16 * h + c;
-                            if (n1 < pfa::kN1 && n2 < pfa::kN2)
-                                s_stage[pfa::time_index(n1, n2) * kPad + w] = acc[u][h][q] * out_scale;
-                        }
+                        for (int h = 0; h < 3; ++h)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                const int n1 = 16 * u + 4 * g + q, n2 = 16 * h + c;
+                                if (n1 < pfa::kN1 && n2 < pfa::kN2)
+                                    s_stage[pfa::time_index(n1, n2) * kPad + w] = acc[p][u][h][q] * out_scale;
+                            }
+                }
+                __syncthreads();
+                write_rows<W>(s_stage, d, pi + p, chunk, tid, d.acc != 0);
             }
-            __syncthreads();
-            write_rows<W>(s_stage, d, pi, chunk, tid, d.acc != 0);
         }
     }
 }
@@ -2223,8 +2308,8 @@ __global__ __launch_bounds__(kSynthThreads) void k_fd_synth(const ReqDesc *__res
                     wv = make_float2(wv.x * c1 - wv.y * s1, wv.x * s1 + wv.y * c1);
                 }
             }
-            // fragment position of frequency j: (a, b') = (j mod 31, j mod 33)
-            const int a = j % pfa::kN1, bb = j % pfa::kN2;
+            // fragment position of frequency j: row j mod 31, column (j - 1) mod 33
+            const int a = j % pfa::kN1, bb = (j + pfa::kN2 - 1) % pfa::kN2;
             const int t = bb >> 4, cc = bb & 15, s31 = a >> 4, gg = (a >> 2) & 3, jj = a & 3;
             const int unit = t < 2 ? (2 * t + s31) * 64 + 16 * gg + cc : pfa::kTailUnit + 4 * s31 + gg;
             const float2 wm1 = make_float2(c2 - 1.f, s2);

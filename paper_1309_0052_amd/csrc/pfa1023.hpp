@@ -27,16 +27,17 @@
 //
 // Layouts (t < 3 tiles of the 33-dimension, s < 2 K steps of the 31-one):
 //   spectrum fragment (t, s): lane (g, c) holds the complex values at
-//     a = 16 s + 4 g + j, b = 16 t + c, j < 4, as [re j=0..3, im j=0..3] (8 FP16)
-//   31-pass output D31[t][n]: lane (g, c), r: Z_part[n1' = 16 (n & 1) + c][b = 16 t + 4 g + r],
+//     a = 16 s + 4 g + j, column p = 16 t + c (b = (p + 1) mod 33), j < 4, as
+//     [re j=0..3, im j=0..3] (8 FP16)
+//   31-pass output D31[t][n]: lane (g, c), r: Z_part[n1' = 16 (n & 1) + c][p = 16 t + 4 g + r],
 //     part = n >> 1 (0 re, 1 im)
-//   33-pass K slots: step t < 3 holds b = 16 t + 4 g + (j & 3), part j >> 2 (the
-//     last step has b = 32 only, in lanes g = 0)
+//   33-pass K slots: step t < 3 holds p = 16 t + 4 g + (j & 3), part j >> 2 (the
+//     last step has p = 32 only, in lanes g = 0)
 //   33-pass output D33[u][v]: lane (g, c), r: row 16 u + 4 g + r of the 31-dimension,
 //     column n2' = 16 (v >> 1) + c, part v & 1 for v < 4; tile v = 4 holds column
 //     32 (re in lane c = 0, im in lane c = 1) in the inverse, and tiles v = 4, 5
 //     column 32 + c (re, im; valid for c = 0) in the forward transform.
-// Padded slots (a = 31, b >= 33) carry zero weights, so they stay zero.
+// Padded slots (a = 31, p >= 33) carry zero weights, so they stay zero.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -47,6 +48,9 @@ namespace pfa {
 
 constexpr int kN1 = 31, kN2 = 33, kLen = 1023;
 constexpr int kKa = 528, kKb = 496;  // frequency map weights
+// Spectra are held by columns p = 0 .. 32 with b = (p + 1) mod 33: the column
+// that fills no tile of 16, p = 32, is then b = 0, whose 33-point weights are 1.
+__host__ __device__ __forceinline__ int column_b(int p) { return p + 1 < kN2 ? p + 1 : 0; }
 // Stored spectra (block spectra, code spectra): fragments (t, s) for t < 2 as
 // 64 lanes x 16 B each (unit (2 t + s) * 64 + lane), then the t = 2 fragments
 // of the c = 0 lanes (unit 256 + 4 s + g); every other lane of t = 2 is zero.
@@ -155,7 +159,7 @@ __device__ __forceinline__ void inverse(const u4 (&a1)[3][2], const InvB &B, f4 
 }
 
 // Forward DFT: out[u][v], 6 column tiles; rows a = 16 u + 4 g + r, columns
-// b = 16 (v >> 1) + c, part v & 1.
+// p = 16 (v >> 1) + c, part v & 1.
 __device__ __forceinline__ void forward(const u4 (&a1)[3][2], const FwdB &B, f4 (&out)[2][6])
 {
     f4 d1[3][4];
@@ -165,9 +169,9 @@ __device__ __forceinline__ void forward(const u4 (&a1)[3][2], const FwdB &B, f4 
     pass33<6>(a2, B.b33, out);
 }
 
-// Time index of (n1, n2) and frequency index of (a, b).
+// Time index of (n1, n2) and frequency index of row a, column p.
 __host__ __device__ __forceinline__ int time_index(int n1, int n2) { return (33 * n1 + 31 * n2) % kLen; }
-__host__ __device__ __forceinline__ int freq_index(int a, int b) { return (kKa * a + kKb * b) % kLen; }
+__host__ __device__ __forceinline__ int freq_index(int a, int p) { return (kKa * a + kKb * (p + 1)) % kLen; }
 
 }  // namespace pfa
 }  // namespace gnss
