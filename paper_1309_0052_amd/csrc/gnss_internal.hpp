@@ -270,7 +270,6 @@ inline int corr_waves(int precision, int pt)
 // instantiated shapes: FP32 tile 1 with 12, 6 or 4 waves (three waves per
 // SIMD), tiles 2 and 4 with 8; the FP16 kernels have one width each
 bool corr_shape_valid(CorrShape c, int precision);
-constexpr int kBoxChunk = 2048;
 constexpr int kPeakThreads = 256;   // threads of the column-max kernel (256-lag blocks)
 constexpr int kArgThreads = 1024;   // threads of the per-PRN argmax kernel
 constexpr int kPeakLags = 16384;    // column maxima it keeps in registers

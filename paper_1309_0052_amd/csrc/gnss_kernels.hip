@@ -458,10 +458,8 @@ __device__ __forceinline__ long long next_item(BatchHdr *h, int stage, long long
 
 // ===========================================================================
 // stage A1: wipe + fold, then the one-chip boxcar
-// F[n] = sum_{t<spc} f[(n+t) mod N], written split by phase:
-// F[vec(k, b, s)][m] = F[spc m + s] (m < 1023), [..][1023] = 0.  A work item is
-// one (request, Doppler, block), done in chunks of kBoxChunk outputs, each
-// wiping the spc - 1 samples past it as a halo.  All integer, exact.
+// F[n] = sum_{t<spc} f[(n+t) mod N], split by phase: F[spc m + s] (m < 1023) at
+// element m of phase s, 0 at m = 1023.  All integer, exact.
 // ===========================================================================
 // Mixing by integer dot products.  A sample as two 16-bit halves (re, im) and
 // a table entry {(cos, sin), (-sin, cos)} give y = x (cos - j sin), added to
@@ -500,153 +498,25 @@ __device__ __forceinline__ s2v load_mix(const GNSS_GLOBAL uint8_t *p, uint32_t o
     }
 }
 
-constexpr int kBoxRun = 8;
-__device__ __forceinline__ int bpad(int i) { return i + (i >> 3); }  // bank-conflict padding
+constexpr int kBfThreads = 512, kBfSlots = 16;
+// The folded samples in LDS, one row of spc per m (the runs the boxcars read),
+// rows an odd number of 8-byte slots apart: no bank conflicts between lanes that
+// read different rows.  row_inv: i / spc as (i row_inv) >> 18, exact below 2^14.
+__device__ __forceinline__ uint32_t row_inv(int spc) { return (spc & 1) ? 0u : (1u << 18) / (uint32_t)spc + 1u; }
+__device__ __forceinline__ int row_pad(int i, uint32_t inv) { return i + (int)(__umul24((uint32_t)i, inv) >> 18); }
+static_assert((kSeg3 + 1) * (kMaxSpc + 1) <= kBfSlots * kXbuf3 && (2 * kSeg3 - 1) * 9 + 8 <= kBfSlots * kXbuf3,
+              "samples and transforms share the LDS");
 
-// Wipe + fold of samples n0 .. n0 + len - 1 (mod N) of block b into s_f,
-// FMT-specialised; the phase of the folded milliseconds advances by N D (mod
-// 2^32) from one to the next.  Same values as wipe_fold_one.  Samples are addressed from
-// the block's first byte (the same pointer in every thread) by 32-bit in-block
-// offsets: a block holds Tc N <= 64 * 16368 samples.
-template <int FMT, int NT>
-__device__ __forceinline__ void box_wipe(const void *samples, int N, int Tc, const uint2 *s_lut, uint32_t D,
-                                         int b, int n0, int len, int shift, int2 *s_f)
-{
-    const uint32_t dN = (uint32_t)N * D;
-    const long long base = (long long)b * Tc * N;
-    // 2-bit packed records: the block may start inside a byte
-    const uint32_t sub = FMT == GNSS_REAL_2BIT_PACKED ? (uint32_t)(base & 3) : 0u;
-    const long long blk_byte = FMT == GNSS_CPLX_I8 ? 2 * base : FMT == GNSS_REAL_I8 ? base : (base >> 2);
-    const GNSS_GLOBAL uint8_t *blk = (const GNSS_GLOBAL uint8_t *)samples + blk_byte;
-    const uint32_t step = FMT == GNSS_CPLX_I8 ? 2u * (uint32_t)N : (uint32_t)N;  // bytes (samples if packed)
-    for (int i = threadIdx.x; i < len; i += NT) {
-        int n = n0 + i - shift;  // shift in [0, N): the block read circularly delayed
-        if (n < 0) n += N;
-        if (n >= N) n -= N;
-        uint32_t ph = (uint32_t)(base + n) * D;
-        // the milliseconds' phases are ph + c N D: additions, not one multiply each
-        asm volatile("" : "+v"(ph));
-        // byte offset (sample index if packed) of millisecond c in the block
-        uint32_t off = FMT == GNSS_CPLX_I8 ? 2u * (uint32_t)n : (uint32_t)n + sub;
-        int yr = 0, yi = 0;
-#pragma unroll 4
-        for (int c = 0; c < Tc; ++c) {
-            mix_add(load_mix<FMT>(blk, off), s_lut[ph >> 22], yr, yi);
-            off += step;
-            ph += dN;
-        }
-        s_f[bpad(i)] = make_int2(yr, yi);
-    }
-}
-
-// LDS chunk buffer of box_item: kBoxChunk + spc - 1 wiped samples, padded
-constexpr int kBoxBuf = (kBoxChunk + kMaxSpc) + (kBoxChunk + kMaxSpc) / 8 + 8;
-
-// The wipe, fold, boxcar and polyphase split of one (Doppler k, block b) item
-// of request d by NT threads: dst[s * kPolyLen + m] = F[spc m + s] for m <
-// 1023 and 0 at m = 1023 (dst: the item's polyphase vectors in F).
-template <int NT, typename DstPtr>
-__device__ __forceinline__ void box_item(const ReqDesc &d, int k, int b, const uint2 *s_lut, int2 *s_f,
-                                         DstPtr dst)
-{
-    const int N = d.N, spc = d.spc;
-    const uint32_t D = d.dk[k];
-    // code-Doppler drift of this (bin, block) in samples, in [0, N): delaying
-    // the folded block by it circularly shifts its correlation by as many lags
-    const int shift = d.cshift ? d.cshift[(long long)k * d.Nnc + b] : 0;
-    for (int n0 = 0; n0 < N; n0 += kBoxChunk) {
-        const int cnt = min(kBoxChunk, N - n0);
-        const int len = cnt + spc - 1;
-        __syncthreads();  // LUT staged / previous chunk's boxcar done
-        if (d.fmt == GNSS_CPLX_I8)
-            box_wipe<GNSS_CPLX_I8, NT>(d.samples, N, d.Tc, s_lut, D, d.b0 + b, n0, len, shift, s_f);
-        else if (d.fmt == GNSS_REAL_I8)
-            box_wipe<GNSS_REAL_I8, NT>(d.samples, N, d.Tc, s_lut, D, d.b0 + b, n0, len, shift, s_f);
-        else
-            box_wipe<GNSS_REAL_2BIT_PACKED, NT>(d.samples, N, d.Tc, s_lut, D, d.b0 + b, n0, len, shift, s_f);
-        __syncthreads();
-        const int n_runs = (cnt + kBoxRun - 1) / kBoxRun;
-        for (int rr = threadIdx.x; rr < n_runs; rr += NT) {
-            const int i0 = rr * kBoxRun;
-            int sx = 0, sy = 0;
-            for (int t = 0; t < spc; ++t) {
-                int2 v = s_f[bpad(i0 + t)];
-                sx += v.x;
-                sy += v.y;
-            }
-            const int n = n0 + i0;
-            int m = n / spc, s = n - m * spc;
-#pragma unroll
-            for (int j = 0; j < kBoxRun; ++j) {
-                const int i = i0 + j;
-                if (i >= cnt) break;
-                dst[s * kPolyLen + m] = make_int2(sx, sy);
-                if (i + 1 < cnt) {
-                    int2 vi = s_f[bpad(i + spc)], vo = s_f[bpad(i)];
-                    sx += vi.x - vo.x;
-                    sy += vi.y - vo.y;
-                }
-                if (++s == spc) {
-                    s = 0;
-                    ++m;
-                }
-            }
-        }
-    }
-    if (threadIdx.x < spc) dst[threadIdx.x * kPolyLen + (kPolyLen - 1)] = make_int2(0, 0);
-}
-
-__global__ __launch_bounds__(256) void k_box(const ReqDesc *__restrict__ R, BatchHdr *H, const long long *pre,
-                                             const uint32_t *lut, int2 *F)
-{
-    __shared__ int2 s_f[kBoxBuf];
-    __shared__ uint2 s_lut[1024];
-    __shared__ long long s_item;
-    stage_mix_lut(s_lut, lut, threadIdx.x, 256);
-    const int n_req = H->n_req;
-    const long long total = H->total[kStBox];
-    const long long *pst = pre + (long long)kStBox * (n_req + 1);
-    bool first = true;
-    for (;;) {
-        const long long it = next_item(H, kStBox, total, &s_item, first);
-        if (it < 0) break;
-        const int r = find_req(pst, n_req, it);
-        const ReqDesc &d = R[r];
-        // (Doppler, block)-major items (dealing them block-major, so that the bins of
-        // a block share its samples in L2, was measured 15% slower)
-        const int kb = (int)(it - first_item(pst, n_req, r));  // < 2^31 by the plan checks
-        const int k = kb / d.Nnc, b = kb - (kb / d.Nnc) * d.Nnc;
-        box_item<256>(d, k, b, s_lut, s_f, F + (d.vec_off + (long long)kb * d.spc) * kPolyLen);
-    }
-}
-
-// ===========================================================================
-// stage A, FP32: wipe, fold, boxcar, polyphase split and forward transforms in
-// one kernel.  A work item is 8192 outputs F[n] at most: one segment (512
-// values of m) of a (Doppler, block) with more than 8 samples per chip, else
-// both.  The 512 threads wipe and fold the item's samples into LDS, sum the
-// boxcars in runs of 16 outputs held in registers, write them back split by
-// (segment, phase) and each wave transforms the segments w and w + 8.  What
-// bounds it is the write of the spectra (24 KB per (Doppler, block, phase));
-// the polyphase values, written and read again by two kernels before, stay in
-// LDS.  78 KB of LDS: two workgroups per CU, so that one's transforms overlap
-// the other's sample loads.  Measured on the
-// weak-signal search (121 bins x 25 blocks x 16 phases, 1.19 GB of spectra):
-// 0.32 ms, 3.7 TB/s, against 0.17 + 0.27 ms for the two kernels it replaces.
-// ===========================================================================
-constexpr int kBfThreads = 512, kBfOut = 8192, kBfRun = 16, kBfSlots = 16;
-static_assert(kBfThreads * kBfRun == kBfOut, "one run per thread");
-__device__ __forceinline__ int bf_pad(int i) { return i + (i >> 4); }  // runs of 16 at stride 17: no bank conflicts
-static_assert((kBfOut + 2 * kMaxSpc) * 17 / 16 + 1 <= kBfSlots * kXbuf3, "samples and transforms share the LDS");
-
-// Wipe + fold of samples n0 + i, i = i0 + tid + 512 j < len (j < 9), of block b
-// into s_f, the arithmetic of box_wipe with the nine samples' loads of a
-// millisecond in flight together.
-template <int FMT>
+// Wipe + fold of samples n0 + i, i = i0 + tid + 512 j < len (j < J), of block b
+// into s_f, the J samples' loads of a millisecond in flight together; the phase
+// of the folded milliseconds advances by N D (mod 2^32) from one to the next.
+// Same values as wipe_fold_one.  Samples are addressed from the block's first byte
+// (the same pointer in every thread) by 32-bit in-block offsets: a block holds
+// Tc N <= 64 * 16368 samples.
+template <int FMT, int J>
 __device__ __forceinline__ void bf_wipe(const ReqDesc &d, const uint2 *s_lut, uint32_t D, int b, int n0, int i0,
-                                        int len, int2 *s_f)
+                                        int len, uint32_t inv, int2 *s_f)
 {
-    constexpr int J = 9;
     const int N = d.N, Tc = d.Tc;
     const uint32_t dN = (uint32_t)N * D;
     const long long base = (long long)b * Tc * N;
@@ -655,27 +525,34 @@ __device__ __forceinline__ void bf_wipe(const ReqDesc &d, const uint2 *s_lut, ui
     const long long blk_byte = FMT == GNSS_CPLX_I8 ? 2 * base : FMT == GNSS_REAL_I8 ? base : (base >> 2);
     const GNSS_GLOBAL uint8_t *blk = (const GNSS_GLOBAL uint8_t *)d.samples + blk_byte;
     const uint32_t step = FMT == GNSS_CPLX_I8 ? 2u * (uint32_t)N : (uint32_t)N;  // bytes (samples if packed)
+    constexpr uint32_t kUnit = FMT == GNSS_CPLX_I8 ? 2u : 1u;
     uint32_t off[J], ph[J];
     int yr[J], yi[J];
+    const int na = n0 + i0 + (int)threadIdx.x;
     const uint32_t ph0 = (uint32_t)(base + n0 + i0 + (int)threadIdx.x) * D;
+    const bool whole = n0 + i0 >= 0 && n0 + i0 + kBfThreads * J <= N;  // no sample past either end
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-        const int i = i0 + (int)threadIdx.x + kBfThreads * j;
-        int n = n0 + i;  // in (-N, 2N): the block read circularly, N D (mod 2^32) of phase back or on
-        uint32_t p = ph0 + (uint32_t)(kBfThreads * j) * D;
-        if (n < 0) {
-            n += N;
-            p += dN;
-        }
-        if (n >= N) {
-            n -= N;
-            p -= dN;
-        }
-        if (i >= len) n = 0;  // not stored
-        ph[j] = p;
-        off[j] = FMT == GNSS_CPLX_I8 ? 2u * (uint32_t)n : (uint32_t)n + sub;
+        ph[j] = ph0 + (uint32_t)(kBfThreads * j) * D;
+        off[j] = kUnit * (uint32_t)(na + kBfThreads * j) + sub;
         yr[j] = 0;
         yi[j] = 0;
+    }
+    if (!whole) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            int n = na + kBfThreads * j;  // in (-N, 2N): the block read circularly, N D (mod 2^32) of phase back or on
+            if (n < 0) {
+                n += N;
+                ph[j] += dN;
+            }
+            if (n >= N) {
+                n -= N;
+                ph[j] -= dN;
+            }
+            if (i0 + (int)threadIdx.x + kBfThreads * j >= len) n = 0;  // not stored
+            off[j] = kUnit * (uint32_t)n + sub;
+        }
     }
 #pragma unroll 1
     for (int c = 0; c < Tc; ++c) {
@@ -690,17 +567,179 @@ __device__ __forceinline__ void bf_wipe(const ReqDesc &d, const uint2 *s_lut, ui
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         const int i = i0 + (int)threadIdx.x + kBfThreads * j;
-        if (i < len) s_f[bf_pad(i)] = make_int2(yr[j], yi[j]);
+        if (i < len) s_f[row_pad(i, inv)] = make_int2(yr[j], yi[j]);
     }
 }
 
+template <int FMT>
+__device__ __forceinline__ void bf_wipe_all(const ReqDesc &d, const uint2 *s_lut, uint32_t D, int b, int n0, int len,
+                                            uint32_t inv, int2 *s_f)
+{
+    int i0 = 0;
+    for (; len - i0 > 4 * kBfThreads; i0 += 8 * kBfThreads) bf_wipe<FMT, 8>(d, s_lut, D, b, n0, i0, len, inv, s_f);
+    for (; len - i0 > kBfThreads; i0 += 4 * kBfThreads) bf_wipe<FMT, 4>(d, s_lut, D, b, n0, i0, len, inv, s_f);
+    // the rest of up to 512 (a part's halo), by the waves that have any of it
+    if (i0 + (int)(threadIdx.x & ~63u) < len) bf_wipe<FMT, 1>(d, s_lut, D, b, n0, i0, len, inv, s_f);
+}
+
+// F[S m + s], s < S, of one m: the sum of the row's S samples, then from one output
+// to the next a sample in (of the next row) and one out.
+template <int S, typename P2>
+__device__ __forceinline__ void bf_boxcar(const int2 *s_f, int m, P2 (&o)[16], int at)
+{
+    constexpr int kRow = S | 1;
+    const int2 *run = s_f + m * kRow;
+    int2 a[S];
+#pragma unroll
+    for (int t = 0; t < S; ++t) a[t] = run[t];
+    int sx = 0, sy = 0;
+#pragma unroll
+    for (int t = 0; t < S; ++t) {
+        sx += a[t].x;
+        sy += a[t].y;
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        o[at + s].x = sx;
+        o[at + s].y = sy;
+        if (s + 1 < S) {
+            const int2 v = run[kRow + s];
+            sx += v.x - a[s].x;
+            sy += v.y - a[s].y;
+        }
+    }
+}
+
+template <int S, typename P2>
+__device__ __forceinline__ void bf_split(int part, P2 *s_x)
+{
+    const int tid = threadIdx.x;
+    const int2 *s_f = (const int2 *)s_x;
+    constexpr int kRuns = S > 8 ? 1 : 2;  // rows m = tid (and 512 + tid, if a part is a whole block)
+    P2 o[16];
+    const bool last = tid == kSeg3 - 1;   // m = 1023 of the second segment is zero
+#pragma unroll
+    for (int q = 0; q < kRuns; ++q) {
+        if (last && (q == 1 || part == 1)) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) o[q * S + s] = P2{0, 0};
+        } else {
+            bf_boxcar<S>(s_f, q * kSeg3 + tid, o, q * S);
+        }
+    }
+    __syncthreads();  // the samples are read
+#pragma unroll
+    for (int s = 0; s < kRuns * S; ++s) s_x[s * kXbuf3 + tid] = o[s];
+}
+
+// The wipe, fold, boxcar and polyphase split of part `part` of (Doppler, block) kb
+// of request d: F[spc m + s] at element m mod 512 of slot s (of a part) or of
+// slot (segment, s) (of a whole block), and 0 for m = 1023.  A part is 8192
+// outputs at most: one segment (512 values of m) with more than 8 samples per
+// chip, else both.  The 512 threads wipe and fold the samples into LDS; each then
+// has the outputs of one or two m, its reads and writes at constant distances (one
+// instance per number of samples per chip), and leaves them by slot.  Vector issue
+// bounds it: with runs of 16 consecutive outputs, each one's slot and element found
+// as it went, it took 0.30 ms on the weak-signal search (121 bins x 25 blocks x
+// 4 ms at 16.368 MHz) where it takes 0.14, the polyphase values' write included.
+// The caller synchronises before it reads the slots.
+template <typename P2>
+__device__ __forceinline__ void bf_front(const ReqDesc &d, int kb, int part, int parts, const uint2 *s_lut, P2 *s_x)
+{
+    const int N = d.N, spc = d.spc;
+    int2 *s_f = (int2 *)s_x;
+    const int k = kb / d.Nnc, b = kb - k * d.Nnc;
+    const uint32_t D = d.dk[k], inv = row_inv(spc);
+    // code-Doppler drift of this (bin, block) in samples, in [0, N): delaying
+    // the folded block by it circularly shifts its correlation by as many lags
+    const int shift = d.cshift ? d.cshift[kb] : 0;
+    const int n0 = part * kSeg3 * spc;  // first output
+    const int len = min(N - n0, parts == 2 ? kSeg3 * spc : N) + spc - 1;
+    __syncthreads();  // the table is staged; the previous item's slots are read
+    if (d.fmt == GNSS_CPLX_I8)
+        bf_wipe_all<GNSS_CPLX_I8>(d, s_lut, D, d.b0 + b, n0 - shift, len, inv, s_f);
+    else if (d.fmt == GNSS_REAL_I8)
+        bf_wipe_all<GNSS_REAL_I8>(d, s_lut, D, d.b0 + b, n0 - shift, len, inv, s_f);
+    else
+        bf_wipe_all<GNSS_REAL_2BIT_PACKED>(d, s_lut, D, d.b0 + b, n0 - shift, len, inv, s_f);
+    __syncthreads();
+    switch (spc) {
+    case 1: bf_split<1>(part, s_x); break;
+    case 2: bf_split<2>(part, s_x); break;
+    case 3: bf_split<3>(part, s_x); break;
+    case 4: bf_split<4>(part, s_x); break;
+    case 5: bf_split<5>(part, s_x); break;
+    case 6: bf_split<6>(part, s_x); break;
+    case 7: bf_split<7>(part, s_x); break;
+    case 8: bf_split<8>(part, s_x); break;
+    case 9: bf_split<9>(part, s_x); break;
+    case 10: bf_split<10>(part, s_x); break;
+    case 11: bf_split<11>(part, s_x); break;
+    case 12: bf_split<12>(part, s_x); break;
+    case 13: bf_split<13>(part, s_x); break;
+    case 14: bf_split<14>(part, s_x); break;
+    case 15: bf_split<15>(part, s_x); break;
+    default: bf_split<16>(part, s_x); break;
+    }
+}
+
+// ===========================================================================
+// stage A, FP16 modes: wipe, fold, boxcar and polyphase split.  One workgroup
+// per (Doppler, block), its parts in turn; the polyphase vectors go out in whole
+// rows.  Bound: vector issue (the wipe's dot products, the boxcar's sliding sums) and
+// the write of 8 bytes per output, which go on at the same time.
+// Weak-signal search, 0.40 GB: 0.146 ms; with chunks of 2048 outputs, each thread's runs
+// of 8 written as they came, 0.158.
+// ===========================================================================
+__global__ __launch_bounds__(kBfThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_box(
+    const ReqDesc *__restrict__ R, const BatchHdr *H, const long long *pre, const uint32_t *lut, int2 *F)
+{
+    __shared__ int2 s_x[kBfSlots * kXbuf3];
+    __shared__ uint2 s_lut[1024];
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    stage_mix_lut(s_lut, lut, tid, kBfThreads);
+    const int n_req = H->n_req;
+    const long long total = H->total[kStBox];
+    const long long *pst = pre + (long long)kStBox * (n_req + 1);
+    for (long long it = xcd_remap(blockIdx.x, gridDim.x); it < total; it += gridDim.x) {
+        const int r = find_req(pst, n_req, it);
+        const ReqDesc &d = R[r];
+        // (Doppler, block)-major items (dealing them block-major, so that the bins of
+        // a block share its samples in L2, was measured 15% slower)
+        const int kb = (int)(it - first_item(pst, n_req, r));  // < 2^31 by the plan checks
+        const int spc = d.spc, parts = bf_parts(spc);
+        for (int part = 0; part < parts; ++part) {
+            bf_front(d, kb, part, parts, s_lut, s_x);
+            __syncthreads();
+            const int slots = parts == 2 ? spc : 2 * spc;
+            for (int slot = w; slot < slots; slot += kBfThreads / 64) {
+                const int sg = parts == 2 ? part : slot / spc, s = parts == 2 ? slot : slot - sg * spc;
+                const int2 *src = s_x + slot * kXbuf3;
+                int2 *dst = F + (d.vec_off + (long long)kb * spc + s) * kPolyLen + sg * kSeg3;
+#pragma unroll
+                for (int j = 0; j < kSeg3 / 64; ++j) dst[l + 64 * j] = src[l + 64 * j];
+            }
+        }
+    }
+}
+
+// ===========================================================================
+// stage A, FP32: wipe, fold, boxcar, polyphase split and forward transforms in
+// one kernel.  A work item is a part of a (Doppler, block) (bf_front); each wave
+// transforms the segments w and w + 8 where that left them in LDS.  What
+// bounds it is the write of the spectra (24 KB per (Doppler, block, phase));
+// the polyphase values, written and read again by two kernels before, stay in
+// LDS.  78 KB of LDS: two workgroups per CU, so that one's transforms overlap
+// the other's sample loads.  Measured on the
+// weak-signal search (121 bins x 25 blocks x 16 phases, 1.19 GB of spectra):
+// 0.29 ms, 4.1 TB/s, against 0.17 + 0.27 ms for the two kernels it replaces.
+// ===========================================================================
 __global__ __launch_bounds__(kBfThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_box_fft(
     const ReqDesc *__restrict__ R, const BatchHdr *H, const long long *pre, const uint32_t *lut, const float2 *twg,
     float4 *G)
 {
     __shared__ float2 s_x[kBfSlots * kXbuf3];
     __shared__ uint2 s_lut[1024];
-    int2 *s_f = (int2 *)s_x;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     stage_mix_lut(s_lut, lut, tid, kBfThreads);
     const int n_req = H->n_req;
@@ -710,68 +749,10 @@ __global__ __launch_bounds__(kBfThreads) __attribute__((amdgpu_waves_per_eu(4)))
     for (long long it = id; it < total; it += gridDim.x) {
         const int r = find_req(pst, n_req, it);
         const ReqDesc &d = R[r];
-        const int N = d.N, spc = d.spc;
-        const int parts = bf_parts(spc);
+        const int spc = d.spc, parts = bf_parts(spc);
         const int local = (int)(it - first_item(pst, n_req, r));
         const int kb = local / parts, part = local - kb * parts;
-        const int k = kb / d.Nnc, b = kb - k * d.Nnc;
-        const uint32_t D = d.dk[k];
-        // code-Doppler drift of this (bin, block) in samples, in [0, N): delaying
-        // the folded block by it circularly shifts its correlation by as many lags
-        const int shift = d.cshift ? d.cshift[kb] : 0;
-        const int n0 = part * kSeg3 * spc;  // first output
-        const int cnt = min(N - n0, parts == 2 ? kSeg3 * spc : N), len = cnt + spc - 1;
-        __syncthreads();  // the table is staged; the previous item's transforms are done
-        for (int i0 = 0; i0 < len; i0 += 9 * kBfThreads) {
-            if (d.fmt == GNSS_CPLX_I8)
-                bf_wipe<GNSS_CPLX_I8>(d, s_lut, D, d.b0 + b, n0 - shift, i0, len, s_f);
-            else if (d.fmt == GNSS_REAL_I8)
-                bf_wipe<GNSS_REAL_I8>(d, s_lut, D, d.b0 + b, n0 - shift, i0, len, s_f);
-            else
-                bf_wipe<GNSS_REAL_2BIT_PACKED>(d, s_lut, D, d.b0 + b, n0 - shift, i0, len, s_f);
-        }
-        __syncthreads();
-        float2 o[kBfRun];
-        const int i0 = tid * kBfRun;
-        if (i0 < cnt) {
-            int sx = 0, sy = 0;
-            const int2 *run = s_f + bf_pad(i0);  // i0 + t at run[bf_pad(t)]; samples past len are not used
-            for (int t = 0; t < spc; ++t) {
-                const int2 v = run[t];
-                sx += v.x;
-                sy += v.y;
-            }
-#pragma unroll
-            for (int j = 0; j < kBfRun; ++j) {
-                o[j] = make_float2((float)sx, (float)sy);
-                if (j + 1 < kBfRun) {
-                    const int2 vi = run[bf_pad(j + spc)], vo = run[j];
-                    sx += vi.x - vo.x;
-                    sy += vi.y - vo.y;
-                }
-                if (j % 4 == 3) phase_barrier();
-            }
-        }
-        __syncthreads();  // the samples are read
-        // slot s of a part, or slot (segment, s) of a whole block: F[spc m + s] at m mod 512
-        if (i0 < cnt) {
-            const int n = n0 + i0;
-            int m = n / spc, s = n - m * spc;
-#pragma unroll
-            for (int j = 0; j < kBfRun; ++j) {
-                if (i0 + j < cnt) {
-                    const int slot = parts == 2 ? s : (m >> 9) * spc + s;
-                    s_x[slot * kXbuf3 + (m & (kSeg3 - 1))] = o[j];
-                }
-                if (++s == spc) {
-                    s = 0;
-                    ++m;
-                }
-            }
-        }
-        // the second segment's value 511 (m = 1023) is zero
-        if (tid < spc && (parts == 1 || part == 1))
-            s_x[(parts == 2 ? tid : spc + tid) * kXbuf3 + kSeg3 - 1] = make_float2(0.f, 0.f);
+        bf_front(d, kb, part, parts, s_lut, s_x);
         int l = tid & 63;
         asm volatile("" : "+v"(l));  // the twiddle addresses are formed here, not hoisted and held
         const Lane3 lw(twg, l);
@@ -3507,8 +3488,8 @@ hipError_t launch_box(const Launch &L, const uint32_t *d_lut, int2 *d_F, int n_c
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || L.total[kStBox] == 0) return e;
     static int cap = 0;
-    if (!cap) cap = occupancy(k_box, 256, n_cu);
-    hipLaunchKernelGGL(k_box, dim3(grid_for(L.total[kStBox], cap, false)), dim3(256), 0, s, L.reqs, L.hdr, L.pre,
+    if (!cap) cap = occupancy(k_box, kBfThreads, n_cu);
+    hipLaunchKernelGGL(k_box, dim3(grid_for(L.total[kStBox], cap, false)), dim3(kBfThreads), 0, s, L.reqs, L.hdr, L.pre,
                        d_lut, d_F);
     return hipGetLastError();
 }
@@ -3587,8 +3568,8 @@ hipError_t launch_batch(const Launch &L, const Tables &T, int2 *d_F, void *d_G, 
         }
     } else if (L.total[kStBox] > 0) {
         static int cap = 0;
-        if (!cap) cap = occupancy(k_box, 256, n_cu);
-        hipLaunchKernelGGL(k_box, dim3(grid_for(L.total[kStBox], cap, false)), dim3(256), 0, s, L.reqs,
+        if (!cap) cap = occupancy(k_box, kBfThreads, n_cu);
+        hipLaunchKernelGGL(k_box, dim3(grid_for(L.total[kStBox], cap, false)), dim3(kBfThreads), 0, s, L.reqs,
                            L.hdr, L.pre, d_lut, d_F);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
