@@ -2931,51 +2931,68 @@ __device__ __forceinline__ void row_inv_column(const float2 *y, int t, int j, fl
 
 // The wipe-off and fold of this thread's samples n = n0 + 2048 a + t + T j
 // (a < NA, j < C) of block b (zero at n >= n1), delayed circularly by shift:
-// the arithmetic of wipe_fold_one with the milliseconds outermost, so that
-// the samples' loads of one millisecond are in flight together.
+// the values of wipe_fold_one, mixed by dot products (mix_add) with the
+// milliseconds outermost, so that the samples' loads of one millisecond are in
+// flight together.  In-block offsets have 32 bits (Tc N <= 64 * 16384 samples), and the
+// phase advances by N D (mod 2^32) from one millisecond to the next.  Vector issue is
+// what it costs: at 10 MHz (121 bins x 25 blocks of 4 ms, P = 16384) the spectra took
+// 0.50 ms with bytes, products and a 64-bit index per sample, and take 0.34.
 template <int FMT, int P, int NA>
-__device__ __forceinline__ void row_fold_fmt(const ReqDesc &d, int b, uint32_t D, int shift, const uint32_t *s_lut,
+__device__ __forceinline__ void row_fold_fmt(const ReqDesc &d, int b, uint32_t D, int shift, const uint2 *s_lut,
                                              int t, int n0, int n1, float2 (&f)[RowFft<P>::C][NA])
 {
     constexpr int C = RowFft<P>::C;
+    constexpr uint32_t kUnit = FMT == GNSS_CPLX_I8 ? 2u : 1u;
     const int N = d.N, Tc = d.Tc;
-    int yr[C][NA], yi[C][NA], m[C][NA];
+    const uint32_t dN = (uint32_t)N * D;
+    const long long base = (long long)(d.b0 + b) * Tc * N;
+    // 2-bit packed records: the block may start inside a byte
+    const uint32_t sub = FMT == GNSS_REAL_2BIT_PACKED ? (uint32_t)(base & 3) : 0u;
+    const long long blk_byte = FMT == GNSS_CPLX_I8 ? 2 * base : FMT == GNSS_REAL_I8 ? base : (base >> 2);
+    const GNSS_GLOBAL uint8_t *blk = (const GNSS_GLOBAL uint8_t *)d.samples + blk_byte;
+    const uint32_t step = kUnit * (uint32_t)N;  // bytes (samples if packed)
+    const uint32_t ph0 = (uint32_t)(base + n0 + t - shift) * D;
+    int yr[C][NA], yi[C][NA];
+    uint32_t off[C][NA], ph[C][NA];
 #pragma unroll
     for (int j = 0; j < C; ++j)
 #pragma unroll
         for (int a = 0; a < NA; ++a) {
             const int n = n0 + 2048 * a + t + RowFft<P>::T * j;
-            int mm = n - shift;
-            if (mm < 0) mm += N;
-            m[j][a] = n < n1 ? mm : -1;
+            int m = n - shift;
+            uint32_t p = ph0 + (uint32_t)(2048 * a + RowFft<P>::T * j) * D;
+            if (m < 0) {
+                m += N;
+                p += dN;
+            }
+            off[j][a] = kUnit * (uint32_t)(n < n1 ? m : 0) + sub;  // (not used past n1)
+            ph[j][a] = p;
             yr[j][a] = 0;
             yi[j][a] = 0;
         }
+#pragma unroll 1
     for (int c = 0; c < Tc; ++c) {
-        const long long base = (long long)((d.b0 + b) * Tc + c) * N;
 #pragma unroll
         for (int j = 0; j < C; ++j)
 #pragma unroll
             for (int a = 0; a < NA; ++a) {
-                if (m[j][a] < 0) continue;
-                const long long ng = base + m[j][a];
-                int xr, xi;
-                load_sample(d.samples, FMT, ng, xr, xi);
-                const uint32_t ph = (uint32_t)(unsigned long long)ng * D;
-                const uint32_t e = s_lut[ph >> 22];
-                const int cs = (int)(int16_t)(e & 0xFFFFu), sn = (int)(int16_t)(e >> 16);
-                yr[j][a] += xr * cs + xi * sn;
-                yi[j][a] += xi * cs - xr * sn;
+                mix_add(load_mix<FMT>(blk, off[j][a]), s_lut[ph[j][a] >> 22], yr[j][a], yi[j][a]);
+                if (FMT == GNSS_REAL_2BIT_PACKED) off[j][a] += step;
+                ph[j][a] += dN;
             }
+        if (FMT != GNSS_REAL_2BIT_PACKED) blk += step;
     }
 #pragma unroll
     for (int j = 0; j < C; ++j)
 #pragma unroll
-        for (int a = 0; a < NA; ++a) f[j][a] = make_float2((float)yr[j][a], (float)yi[j][a]);
+        for (int a = 0; a < NA; ++a) {
+            const bool in = n0 + 2048 * a + t + RowFft<P>::T * j < n1;
+            f[j][a] = in ? make_float2((float)yr[j][a], (float)yi[j][a]) : make_float2(0.f, 0.f);
+        }
 }
 
 template <int P, int NA>
-__device__ __forceinline__ void row_fold(const ReqDesc &d, int b, uint32_t D, int shift, const uint32_t *s_lut, int t,
+__device__ __forceinline__ void row_fold(const ReqDesc &d, int b, uint32_t D, int shift, const uint2 *s_lut, int t,
                                          int n0, int n1, float2 (&f)[RowFft<P>::C][NA])
 {
     if (d.fmt == GNSS_CPLX_I8)
@@ -2999,7 +3016,7 @@ __global__ __launch_bounds__(RowFft<P>::T) void k_gen_spec_rows(const ReqDesc *_
     constexpr int NS = F::kSegRows;
     __shared__ float2 y[P];
     __shared__ float2 s_tw[kTrimTw];
-    uint32_t *s_lut = (uint32_t *)y;
+    uint2 *s_lut = (uint2 *)y;
     stage_twiddles_trim(s_tw, tw, threadIdx.x, F::T);
     const int n_req = H->n_req;
     const long long total = H->total[kStGenX];
@@ -3039,20 +3056,24 @@ __global__ __launch_bounds__(RowFft<P>::T) void k_gen_spec_rows(const ReqDesc *_
             const int kb = (int)(idx - d.n_prn), k = kb / d.Nnc, b = kb - k * d.Nnc;
             const uint32_t D = d.dk[k];
             const int shift = d.cshift ? d.cshift[kb] : 0;
-            for (int i = threadIdx.x; i < 1024; i += F::T) s_lut[i] = lut[i];
+            stage_mix_lut(s_lut, lut, threadIdx.x, F::T);
             __syncthreads();
-            if (d.gen_seg) {
-                // a segment has at most P/3 samples: rows a >= NS are zero
-                float2 g[F::C][NS];
-                row_fold<P, NS>(d, b, D, shift, s_lut, t, n0, min(N, n0 + seg), g);
+            // the first rows only, where the rest is zero
+            auto fold = [&](auto na, int n1) {
+                constexpr int NA = decltype(na)::value;
+                float2 g[F::C][NA];
+                row_fold<P, NA>(d, b, D, shift, s_lut, t, n0, n1, g);
 #pragma unroll
                 for (int j = 0; j < F::C; ++j)
 #pragma unroll
-                    for (int a = 0; a < F::R; ++a) f[j][a] = a < NS ? g[j][a < NS ? a : 0] : make_float2(0.f, 0.f);
-            } else {
-                // N <= M/2 (zeros above, so none at n + P), or N = M
-                row_fold<P, F::R>(d, b, D, shift, s_lut, t, 0, N, f);
-            }
+                    for (int a = 0; a < F::R; ++a) f[j][a] = a < NA ? g[j][a < NA ? a : 0] : make_float2(0.f, 0.f);
+            };
+            if (d.gen_seg)  // a segment has at most P/3 samples: rows a >= NS are zero
+                fold(std::integral_constant<int, NS>(), min(N, n0 + seg));
+            else if (2 * N <= P)  // M = P
+                fold(std::integral_constant<int, F::R / 2>(), N);
+            else  // N = M, or N <= M/2 = P (zeros above, so none at n + P)
+                fold(std::integral_constant<int, F::R>(), N);
             dst = (float4 *)(gen + d.gen_x_off + (long long)kb * M) + h * (P / 2);
             __syncthreads();  // the carrier table is read
         }
