@@ -47,8 +47,11 @@ G_VEC_BYTES = {"fp32": 24576, "fp16": 8192, "fp16pfa": 4224}
 # bytes of one polyphase vector in memory before its transform (FP32 keeps it in LDS)
 F_VEC_BYTES = {"fp32": 0, "fp16": 8192, "fp16pfa": 8192}
 # matrix-core flops of one 1023-point inverse transform in the exact-length
-# mode: 54 16x16x32 FP16 products of 16384 flops each
+# mode with every tile padded: 54 16x16x32 FP16 products of 16384 flops each
+# (mfma_flops_issued_per_launch, mfma_issued_frac count these); the kernel keeps
+# the 33rd column out of the tiles and runs 36.5 (mfma_executed_frac)
 PFA_MFMA_FLOPS = 54 * 16384
+PFA_MFMA_EXECUTED = 36.5 * 16384
 
 
 def precision_const(G, name: str) -> int:
@@ -67,6 +70,7 @@ def corr_roofline(prec: str, flops: float, corr_ms: float, traffic, transforms: 
         issued = transforms * PFA_MFMA_FLOPS
         r["mfma_flops_issued_per_launch"] = issued
         r["mfma_issued_frac"] = round(issued / (corr_ms / 1e3) / 1e12 / peak, 4)
+        r["mfma_executed_frac"] = round(transforms * PFA_MFMA_EXECUTED / (corr_ms / 1e3) / 1e12 / peak, 4)
     return r
 
 

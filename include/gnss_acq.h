@@ -18,9 +18,10 @@
  *    per millisecond at most 16384 (the paper sizes its replica loops by the
  *    recording's sampling frequency, Sec. 3); larger N gives GNSS_ENOTSUP.
  *    At fs = k * 1.023 MHz with k <= 16 (spc = k samples per chip) the
- *    search uses the polyphase form on 2048-point (FP32, FP16) or 1023-point
- *    (GNSS_FP16_PFA) transforms; at every other rate it correlates each
- *    block on zero-padded FP32 transforms of length M = 2^ceil(log2 2N),
+ *    search uses the polyphase form on 1536-point (FP32, two segments),
+ *    2048-point (FP16) or 1023-point (GNSS_FP16_PFA) transforms; at every
+ *    other rate it correlates each block on zero-padded FP32 transforms of
+ *    length M = 2^ceil(log2 2N), or M/2 in two segments where they fit,
  *    whatever the context's precision.
  *  - Doppler bins f_k = lo + k*step (IEEE double, as written), k = 0..n_dopp-1,
  *    n_dopp = floor((hi - lo)/step + 1e-9) + 1 (both ends inclusive).

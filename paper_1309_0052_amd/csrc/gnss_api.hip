@@ -2,7 +2,7 @@
 //
 // A context owns one device, one HIP stream (default priority), the
 // device-resident tables built once at creation (carrier LUT, C/A codes, FFT
-// twiddles, the 2048-point code spectra of all 37 PRNs) and workspaces that
+// twiddles, the code spectra of all 37 PRNs) and workspaces that
 // grow on demand under an HBM budget.  The device keeps every intermediate
 // of a request (the paper keeps intermediate results on the GPU and batches
 // the whole coherent integration, Sec. 5); a host request crosses the bus
@@ -177,7 +177,7 @@ int make_plan(const gnss_request *r, gnss::Plan &p, bool need_outputs)
     // times T_coh_ms (fold) times spc <= 16 (boxcar) stays below 2^31 up to 64 ms
     if (r->T_coh_ms < 1 || r->T_coh_ms > 64) return set_err(GNSS_EINVAL, "T_coh_ms outside [1, 64]");
     if (r->N_noncoh < 1 || r->N_noncoh > 100000) return set_err(GNSS_EINVAL, "N_noncoh outside [1, 100000]");
-    // k * 1.023 MHz (k <= 16): the polyphase form on 2048-point or 1023-point
+    // k * 1.023 MHz (k <= 16): the polyphase form on 1536-, 2048- or 1023-point
     // transforms; any other whole number of kHz up to N = 16384: zero-padded
     // transforms of length M = 2^ceil(log2(2N))
     p.gen = (fs % 1023000 != 0 || fs / 1023000 > gnss::kMaxSpc) ? 1 : 0;
