@@ -3837,13 +3837,16 @@ __device__ __forceinline__ long long track_pass(const GNSS_GLOBAL uint8_t *p, ui
     auto sample = [&](s2v x) {
 #pragma unroll
         for (int cc = 0; cc < kTrackCG; ++cc) {
-            // mix_add onto 0; in asm, as the builtin takes the form that adds in
-            // place and needs its accumulators cleared (and so that the compiler does
-            // not distribute the +-1 factors below into the products)
+            // mix_add onto 0.  |y| is far from saturating; with the clamp bit the
+            // instruction is the three-operand one, which takes the 0 as a constant
+            // (the other form adds in place and needs its accumulators cleared).  From
+            // the builtin, so that the compiler sees a dot product: its result must not
+            // be read by another kind of vector instruction within three wait states.
             const uint2 e = s_lut[ph[cc] >> 22];
-            int yr, yi;
-            asm("v_dot2_i32_i16 %0, %1, %2, 0" : "=v"(yr) : "v"(x), "v"(e.x));
-            asm("v_dot2_i32_i16 %0, %1, %2, 0" : "=v"(yi) : "v"(x), "v"(e.y));
+            int yr = __builtin_amdgcn_sdot2(x, __builtin_bit_cast(s2v, e.x), 0, true);
+            int yi = __builtin_amdgcn_sdot2(x, __builtin_bit_cast(s2v, e.y), 0, true);
+            // keeps the compiler from distributing the +-1 factors below into the products
+            asm("" : "+v"(yr), "+v"(yi));
             const int8_t *row = s_sign[cc];
             const int se = row[(uint32_t)((q[cc] + qe[cc]) >> 32)], sp = row[(uint32_t)(q[cc] >> 32) + 1];
             const int sl = row[(uint32_t)((q[cc] + ql[cc]) >> 32)];
