@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/gnss_acq.h"
+#include "general_rate.hpp"
 
 namespace gnss {
 
@@ -56,44 +57,6 @@ struct Plan {
     int64_t grid_elems() const { return (int64_t)n_prn * n_dopp * N; }
     int64_t n_vec() const { return gen ? 0 : (int64_t)n_dopp * Nnc * spc; }
 };
-
-// General rates: N <= kGenMaxN samples per ms, transforms of length
-// M = 2^ceil(log2(2N)) <= 2 kGenLds (M = N when N is a power of two) done as
-// one (M <= kGenLds) or two (M = 2 kGenLds, even and odd bins) transforms of
-// at most kGenLds points in a workgroup's LDS.
-constexpr int kGenMaxN = 16384;
-constexpr int kGenLds = 16384;
-constexpr int kGenTwLen = 2 * kGenLds;  // twiddle table W_32768^j, j < 32768
-constexpr int kGenThreads = 1024;
-inline int gen_transform_len(int N)
-{
-    // N a power of two (>= 64): the length-N circular correlation is the
-    // N-point one, no padding needed
-    if (N >= 64 && (N & (N - 1)) == 0) return N;
-    int M = 64;
-    while (M < 2 * N) M *= 2;
-    return M;
-}
-
-// Two segments of the block on transforms of half the length (see the
-// general-rate kernels): each segment has at most gen_segment(N) samples, and
-// its correlation at N lags fits M / 2 points.  The shortest transform has 64.
-inline __host__ __device__ int gen_segment(int N) { return (N + 1) / 2; }
-inline bool gen_two_segments(int N, int M) { return M > N && M >= 128 && N + gen_segment(N) <= M / 2; }
-// PRNs per correlation workgroup at transform length P, in rows
-constexpr int gen_group(int P) { return P == 4096 ? 2 : 1; }
-// Whether a request's transforms of P points run as rows (see the
-// general-rate kernels).  At 4096 points a row workgroup does two of a CU's
-// six transforms with four waves, a one-piece one its CU's only transform
-// with sixteen: up to one item per CU the latter ends sooner (N = 2000, 10
-// blocks, 168 items: 88 us against 121), above that the former (1952 items:
-// 233 us against 406; 3872 items of 25 blocks: 0.79 ms against 1.81).  The
-// rule takes only the request's own sizes, so its results do not depend on
-// its batch.
-inline bool gen_in_rows(int P, int n_prn, int n_dopp)
-{
-    return P > 4096 || (P == 4096 && (long long)n_prn * n_dopp > 256);
-}
 
 // one-time tables
 hipError_t launch_gold_codes(uint8_t *d_codes /*[38][1023], row = prn*/, hipStream_t s);

@@ -2585,20 +2585,15 @@ __global__ __launch_bounds__(kGenThreads) void k_gen_spec(const ReqDesc *__restr
         const int S = d.gen_seg ? 2 : 1, seg = d.gen_seg ? gen_segment(N) : N;
         const long long local = it - first_item(pst, n_req, r);
         const long long idx = local / S;
-        const int h = (int)(local - idx * S), n0 = h * seg;
+        const int h = (int)(local - idx * S), n0 = h * seg, n1 = min(N, n0 + seg);
         float2 *dst;
         __syncthreads();  // the tables are staged; the previous item's outputs are read
         if (idx < d.n_prn) {
             const uint8_t *code = codes + (long long)d.prns[idx] * kCodeLen;
             dst = gen + d.gen_c_off + idx * M + h * P;
             for (int j = threadIdx.x; j < P; j += kGenThreads) {
-                float v = 0.f;
-                if (j < seg + N) {
-                    int n = j + n0;  // below 2N
-                    if (n >= N) n -= N;
-                    v = code[gen_chip(n, N)] ? -1.f : 1.f;
-                }
-                x[gx(j)] = make_float2(v, 0.f);
+                const int n = gen_code_sample(j, n0, n1, N);
+                x[gx(j)] = make_float2(n < 0 ? 0.f : code[gen_chip(n, N)] ? -1.f : 1.f, 0.f);
             }
         } else {
             const int kb = (int)(idx - d.n_prn), k = kb / d.Nnc, b = kb - k * d.Nnc;
@@ -2606,7 +2601,6 @@ __global__ __launch_bounds__(kGenThreads) void k_gen_spec(const ReqDesc *__restr
             const int shift = d.cshift ? d.cshift[kb] : 0;
             dst = gen + d.gen_x_off + (long long)kb * M + h * P;
             // samples n0 .. n1 - 1 at [0, n1 - n0), zero above
-            const int n1 = min(N, n0 + seg);
 #pragma unroll 2
             for (int j = threadIdx.x; j < P; j += kGenThreads) {
                 float2 f = make_float2(0.f, 0.f);
@@ -3029,7 +3023,7 @@ __global__ __launch_bounds__(RowFft<P>::T) void k_gen_spec_rows(const ReqDesc *_
         const int S = d.gen_seg ? 2 : 1, seg = d.gen_seg ? gen_segment(N) : N;
         const long long local = it - first_item(pst, n_req, r);
         const long long idx = local / S;
-        const int h = (int)(local - idx * S), n0 = h * seg;
+        const int h = (int)(local - idx * S), n0 = h * seg, n1 = min(N, n0 + seg);
         const bool halves = P == kGenLds && !d.gen_seg && M > P;
         const int t = opaque_tid();
         float2 f[F::C][F::R], wb[F::C];
@@ -3038,10 +3032,8 @@ __global__ __launch_bounds__(RowFft<P>::T) void k_gen_spec_rows(const ReqDesc *_
         if (idx < d.n_prn) {
             const uint8_t *code = codes + (long long)d.prns[idx] * kCodeLen;
             auto cc = [&](int j) -> float {
-                if (j >= seg + N) return 0.f;
-                int n = j + n0;  // below 2N
-                if (n >= N) n -= N;
-                return code[gen_chip(n, N)] ? -1.f : 1.f;
+                const int n = gen_code_sample(j, n0, n1, N);
+                return n < 0 ? 0.f : code[gen_chip(n, N)] ? -1.f : 1.f;
             };
 #pragma unroll
             for (int j = 0; j < F::C; ++j)
@@ -3059,7 +3051,7 @@ __global__ __launch_bounds__(RowFft<P>::T) void k_gen_spec_rows(const ReqDesc *_
             stage_mix_lut(s_lut, lut, threadIdx.x, F::T);
             __syncthreads();
             // the first rows only, where the rest is zero
-            auto fold = [&](auto na, int n1) {
+            auto fold = [&](auto na) {
                 constexpr int NA = decltype(na)::value;
                 float2 g[F::C][NA];
                 row_fold<P, NA>(d, b, D, shift, s_lut, t, n0, n1, g);
@@ -3069,11 +3061,11 @@ __global__ __launch_bounds__(RowFft<P>::T) void k_gen_spec_rows(const ReqDesc *_
                     for (int a = 0; a < F::R; ++a) f[j][a] = a < NA ? g[j][a < NA ? a : 0] : make_float2(0.f, 0.f);
             };
             if (d.gen_seg)  // a segment has at most P/3 samples: rows a >= NS are zero
-                fold(std::integral_constant<int, NS>(), min(N, n0 + seg));
+                fold(std::integral_constant<int, NS>());
             else if (2 * N <= P)  // M = P
-                fold(std::integral_constant<int, F::R / 2>(), N);
+                fold(std::integral_constant<int, F::R / 2>());
             else  // N = M, or N <= M/2 = P (zeros above, so none at n + P)
-                fold(std::integral_constant<int, F::R>(), N);
+                fold(std::integral_constant<int, F::R>());
             dst = (float4 *)(gen + d.gen_x_off + (long long)kb * M) + h * (P / 2);
             __syncthreads();  // the carrier table is read
         }
