@@ -1860,7 +1860,7 @@ __global__ __launch_bounds__(64 * kCorrWavesX) void k_corr_x(const ReqDesc *__re
     constexpr int kPad = W + 1;
     constexpr int NP = PAIRS ? 1 : 2;  // PRNs a wave works on at a time
     __shared__ pfa::u4 s_c[NP * pfa::kUnits];
-    __shared__ float s_stage[1024 * kPad];
+    __shared__ __align__(16) float s_stage[1024 * kPad];  // blocks_x keeps its 33rd column there, 16 bytes at a time
     __shared__ pfa::u4 s_g[W * 2 * kXBuf];  // two block spectra per wave
     __shared__ long long s_item;
     const int tid = threadIdx.x;
