@@ -71,15 +71,16 @@ int mark_use(Workspace &w, hipStream_t s)
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     HIP_TRY(hipStreamIsCapturing(s, &st));
     if (st != hipStreamCaptureStatusNone) return GNSS_OK;
-    if (!w.use_ev) HIP_TRY(hipEventCreateWithFlags(&w.use_ev, kUseEventFlags));
-    HIP_TRY(hipEventRecord(w.use_ev, s));
-    w.used = true;
+    hipEvent_t &ev = w.use_ev[w.by_arg];
+    if (!ev) HIP_TRY(hipEventCreateWithFlags(&ev, kUseEventFlags[w.by_arg]));
+    HIP_TRY(hipEventRecord(ev, s));
+    w.last_use = ev;
     return GNSS_OK;
 }
 
 int ensure_ws(gnss_ctx *c, Workspace &w, DevBuf &b, size_t bytes)
 {
-    return ensure(c, b, bytes, w.used ? w.use_ev : nullptr);
+    return ensure(c, b, bytes, w.last_use);
 }
 
 int ensure(gnss_ctx *c, DevBuf &b, size_t bytes, hipEvent_t wait_ev)
@@ -132,17 +133,19 @@ void release(gnss_ctx *c, DevBuf &b)
 void release_ws(gnss_ctx *c, Workspace &w)
 {
     if (w.stage_ev) (void)hipEventSynchronize(w.stage_ev);
-    if (w.use_ev && w.used) (void)hipEventSynchronize(w.use_ev);
+    if (w.last_use) (void)hipEventSynchronize(w.last_use);
     for (DevBuf *b : {&w.F, &w.G, &w.Q, &w.K, &w.part, &w.grid, &w.meta, &w.samples, &w.peaks, &w.tmeta, &w.tout})
         release(c, *b);
     if (w.h_stage) (void)hipHostFree(w.h_stage);
     if (w.stage_ev) (void)hipEventDestroy(w.stage_ev);
-    if (w.use_ev) (void)hipEventDestroy(w.use_ev);
+    for (hipEvent_t &ev : w.use_ev) {
+        if (ev) (void)hipEventDestroy(ev);
+        ev = nullptr;
+    }
     w.h_stage = nullptr;
     w.h_stage_cap = 0;
     w.stage_ev = nullptr;
-    w.use_ev = nullptr;
-    w.used = false;
+    w.last_use = nullptr;
 }
 
 // ---------------------------------------------------------------------------
@@ -481,8 +484,8 @@ int stage_batch(gnss_ctx *c, Workspace &w, BatchHost &B, hipStream_t s, gnss::La
         B.d[r].cshift = B.cshift_off[r] >= 0 ? (const int32_t *)(dm + ml.cshift) + B.cshift_off[r] : nullptr;
     }
     unsigned char *h;
-    const bool by_arg = mb <= gnss::kMetaArgBytes && !w.staged_meta;
-    if (by_arg) {
+    w.by_arg = mb <= gnss::kMetaArgBytes && !w.staged_meta;
+    if (w.by_arg) {
         h = w.meta_arg;
     } else {
         // pinned staging: wait until the previous copy out of it has finished
@@ -507,7 +510,7 @@ int stage_batch(gnss_ctx *c, Workspace &w, BatchHost &B, hipStream_t s, gnss::La
     memcpy(h + ml.desc, B.d.data(), (size_t)B.n * sizeof(gnss::ReqDesc));
     if (!B.dk.empty()) memcpy(h + ml.dk, B.dk.data(), B.dk.size() * sizeof(uint32_t));
     if (!B.cshift.empty()) memcpy(h + ml.cshift, B.cshift.data(), B.cshift.size() * sizeof(int32_t));
-    if (by_arg) {
+    if (w.by_arg) {
         HIP_TRY(gnss::launch_meta(h, mb, w.meta.p, s));
     } else {
         HIP_TRY(hipMemcpyAsync(w.meta.p, h, mb, hipMemcpyHostToDevice, s));
@@ -763,7 +766,7 @@ int ctx_init_tables(gnss_ctx *c)
     HIP_TRY(hipHostMalloc(&c->ws_na.h_stage, GNSS_NOALLOC_META_BYTES, hipHostMallocDefault));
     c->ws_na.h_stage_cap = GNSS_NOALLOC_META_BYTES;
     HIP_TRY(hipEventCreateWithFlags(&c->ws_na.stage_ev, hipEventDisableTiming));
-    HIP_TRY(hipEventCreateWithFlags(&c->ws_na.use_ev, kUseEventFlags));
+    for (int i = 0; i < 2; ++i) HIP_TRY(hipEventCreateWithFlags(&c->ws_na.use_ev[i], kUseEventFlags[i]));
     return GNSS_OK;
 }
 

@@ -39,8 +39,12 @@ struct DevBuf {
 
 // The events that say when a workspace's buffers are idle order nothing but the
 // freeing of those buffers: no host read and no other device waits on them, so
-// they need no write-back of the caches to the host.
-constexpr unsigned kUseEventFlags = hipEventDisableTiming | hipEventDisableSystemFence;
+// they need no write-back of the caches to the host.  A call whose metadata was a
+// kernel argument is marked without one (1.5 us less of a run of such calls).  A
+// call whose metadata was copied is marked with one: the next such call's copy
+// waits for the marker, and behind a lighter one it starts later (100 tracking
+// records of 2 ms: 35 us a call against 38).
+constexpr unsigned kUseEventFlags[2] = {hipEventDisableTiming, hipEventDisableTiming | hipEventDisableSystemFence};
 
 // Device buffers of one in-flight batch and the pinned staging of its
 // metadata.
@@ -51,9 +55,12 @@ struct Workspace {
     size_t h_stage_cap = 0;
     hipEvent_t stage_ev = nullptr;
     // recorded after the last enqueued work that uses these buffers: growing a
-    // buffer waits for it (not for the whole device)
-    hipEvent_t use_ev = nullptr;
-    bool used = false;
+    // buffer waits for it (not for the whole device).  One event after calls
+    // with copied metadata, one after calls with it as an argument
+    // (kUseEventFlags); last_use is the one recorded last.
+    hipEvent_t use_ev[2] = {nullptr, nullptr};
+    hipEvent_t last_use = nullptr;
+    bool by_arg = false;  // how the metadata staged last went to the device
     // metadata always through the pinned staging (a graph's copy node reads it)
     bool staged_meta = false;
     alignas(16) unsigned char meta_arg[gnss::kMetaArgBytes];  // metadata passed as a kernel argument
@@ -176,7 +183,7 @@ size_t sample_bytes(int fmt, size_t n);
 int ensure(gnss_ctx *c, DevBuf &b, size_t bytes, hipEvent_t wait_ev = nullptr);
 // ensure() for a buffer of workspace w
 int ensure_ws(gnss_ctx *c, Workspace &w, DevBuf &b, size_t bytes);
-// Records w.use_ev on s after work that uses w's buffers (not while s is
+// Records w.last_use on s after work that uses w's buffers (not while s is
 // being captured into a graph, whose workspace never grows).
 int mark_use(Workspace &w, hipStream_t s);
 // True when the countdown reaches this call (failure injection).

@@ -112,8 +112,8 @@ static int track_enqueue(gnss_ctx *c, Workspace &w, const gnss_track_request *re
     const size_t mb = align256(off_ch + ch.size() * sizeof(gnss::TrackCh));
     if ((rc = ensure_ws(c, w, w.tmeta, mb))) return rc;
     unsigned char *h;
-    const bool by_arg = mb <= gnss::kMetaArgBytes;
-    if (by_arg) {
+    w.by_arg = mb <= gnss::kMetaArgBytes;
+    if (w.by_arg) {
         h = w.meta_arg;
     } else {
         if (w.stage_ev) HIP_TRY(hipEventSynchronize(w.stage_ev));
@@ -131,7 +131,7 @@ static int track_enqueue(gnss_ctx *c, Workspace &w, const gnss_track_request *re
     memcpy(h, d.data(), (size_t)n * sizeof(gnss::TrackDesc));
     memcpy(h + off_pre, pre.data(), (size_t)(n + 1) * sizeof(long long));
     memcpy(h + off_ch, ch.data(), ch.size() * sizeof(gnss::TrackCh));
-    if (by_arg) {
+    if (w.by_arg) {
         HIP_TRY(gnss::launch_meta(h, mb, w.tmeta.p, s));
     } else {
         HIP_TRY(hipMemcpyAsync(w.tmeta.p, h, mb, hipMemcpyHostToDevice, s));
