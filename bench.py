@@ -74,6 +74,20 @@ def corr_roofline(prec: str, flops: float, corr_ms: float, traffic, transforms: 
     return r
 
 
+def general_kernel(N: int, items: int) -> str:
+    """The correlation kernel of a search at N samples per ms, no multiple of the chip
+    rate, with `items` (PRN, Doppler bin) pairs: transforms of P points run in rows of
+    2048 above 4096 points, and at 4096 with more than 256 items."""
+    M = 64
+    while M < 2 * N:
+        M *= 2
+    if N >= 64 and N & (N - 1) == 0:
+        M = N
+    two = M > N and M >= 128 and N + (N + 1) // 2 <= M // 2
+    P = M // 2 if two else min(M, 16384)
+    return "k_gen_corr_rows" if P > 4096 or (P == 4096 and items > 256) else "k_gen_corr"
+
+
 def kernel_source_hash() -> str:
     h = hashlib.sha1()
     for p in sorted(glob.glob(os.path.join(ROOT, "paper_1309_0052_amd", "csrc", "*"))):
@@ -326,9 +340,7 @@ def main():
         # a rate that is not a multiple of the chip rate: the zero-padded FP32
         # transforms in every precision
         roofline = corr_roofline("fp32", units * flops_unit, corr_ms, read_traffic("gen_corr", wl), 0)
-        # N > 2048 (and many items from N = 1366 on): transforms in rows of 2048 points;
-        # else the radix-8 kernel of its length
-        roofline["kernel"] = "k_gen_corr_rows" if N > 2048 or (N > 1365 and n_prn * nd > 256) else "k_gen_corr"
+        roofline["kernel"] = general_kernel(N, n_prn * nd)
     else:
         kern = CORR_KERNEL[args.precision]
         roofline = corr_roofline(args.precision, units * flops_unit, corr_ms, read_traffic(kern[2:], wl),
