@@ -347,8 +347,9 @@ int gnss_nco_lut(gnss_ctx *ctx, int16_t *d_cos, int16_t *d_sin, void *stream);
  * 16384), GNSS_ENOMEM, GNSS_EDEVICE. */
 int gnss_wipe_fold(gnss_ctx *ctx, const gnss_request *req, int32_t *d_out, void *stream);
 
-/* The search's own first stage, run alone with the kernel and launch the
- * search uses: carrier NCO and first mixing stage (Sec. 3 Fig. 2), coherent
+/* The search's own first stage, run alone (the kernel of the FP16 precisions'
+ * searches; an FP32 search runs the same code in front of its forward
+ * transforms, in one kernel): carrier NCO and first mixing stage (Sec. 3 Fig. 2), coherent
  * fold of each block (block processing, Sec. 4), then the one-chip boxcar and
  * polyphase split that turn the length-N correlation into spc length-1023
  * ones.  With f_kb the folded block of gnss_wipe_fold, delayed circularly by

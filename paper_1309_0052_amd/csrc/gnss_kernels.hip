@@ -504,6 +504,7 @@ constexpr int kBfThreads = 512, kBfSlots = 16;
 // read different rows.  row_inv: i / spc as (i row_inv) >> 18, exact below 2^14.
 __device__ __forceinline__ uint32_t row_inv(int spc) { return (spc & 1) ? 0u : (1u << 18) / (uint32_t)spc + 1u; }
 __device__ __forceinline__ int row_pad(int i, uint32_t inv) { return i + (int)(__umul24((uint32_t)i, inv) >> 18); }
+static_assert(2 * (kBfSlots * kXbuf3 + 1024) * 8 <= 160 * 1024, "two workgroups of k_box_fft per CU");
 static_assert((kSeg3 + 1) * (kMaxSpc + 1) <= kBfSlots * kXbuf3 && (2 * kSeg3 - 1) * 9 + 8 <= kBfSlots * kXbuf3,
               "samples and transforms share the LDS");
 
@@ -571,6 +572,10 @@ __device__ __forceinline__ void bf_wipe(const ReqDesc &d, const uint2 *s_lut, ui
     }
 }
 
+// In batches of 8, 4 and 1 samples per thread: 8 loads in flight while more than 4 x
+// 512 samples are left.  At 4, 8 and 16 samples per chip the parts are whole batches;
+// elsewhere a batch's rest is mixed and not stored (a quarter of it at 3 samples per
+// chip and of the first part at 9 and 12, half at 1).
 template <int FMT>
 __device__ __forceinline__ void bf_wipe_all(const ReqDesc &d, const uint2 *s_lut, uint32_t D, int b, int n0, int len,
                                             uint32_t inv, int2 *s_f)
@@ -729,8 +734,8 @@ __global__ __launch_bounds__(kBfThreads) __attribute__((amdgpu_waves_per_eu(4)))
 // transforms the segments w and w + 8 where that left them in LDS.  What
 // bounds it is the write of the spectra (24 KB per (Doppler, block, phase));
 // the polyphase values, written and read again by two kernels before, stay in
-// LDS.  78 KB of LDS: two workgroups per CU, so that one's transforms overlap
-// the other's sample loads.  Measured on the
+// LDS.  80 KB of LDS, half of a CU's to the byte: two workgroups per CU, so that
+// one's transforms overlap the other's sample loads.  Measured on the
 // weak-signal search (121 bins x 25 blocks x 16 phases, 1.19 GB of spectra):
 // 0.29 ms, 4.1 TB/s, against 0.17 + 0.27 ms for the two kernels it replaces.
 // ===========================================================================
@@ -2380,11 +2385,12 @@ __global__ __launch_bounds__(kSynthThreads) void k_fd_synth(const ReqDesc *__res
 //   X[2k] = DFT_P(x[j] + x[j + P])[k],  X[2k + 1] = DFT_P((x[j] - x[j + P]) W_M^j)[k],
 // and the inverse's upper half (the only outputs needed, as N <= M/2) is
 //   out[P + k] = A[k] - W_M^-k B[k],  A = IDFT_P(Z even bins), B = IDFT_P(Z odd bins).
-// P <= 2048: in-place radix-8 passes and one radix-2 or 4 pass in a
-// 1024-thread workgroup, decimation in frequency forward (natural order in,
+// In one piece (P <= 2048, and P = 4096 with few items: gen_in_rows): in-place
+// radix-8 passes and one radix-2 or 4 pass in a 1024-thread workgroup, decimation in frequency forward (natural order in,
 // digit-reversed out) and the exact adjoint inverse (digit-reversed in,
 // natural out), so spectra are multiplied in the order they are stored.
-// P = 4096 to 16384: four-step P/2048 x 2048 transforms (below).
+// In rows (P = 4096 with many items, 8192 and 16384): four-step P/2048 x 2048
+// transforms (below).
 // ===========================================================================
 
 // Radix of the LDS passes (a radix-16 butterfly with its twiddles needs about
@@ -2546,10 +2552,10 @@ __device__ __forceinline__ int opaque_tid()
     return t;
 }
 
-// The general-rate kernels are instantiated per transform length P <= 2048
-// (LDS sized by P, so smaller transforms share a CU) and launched once for
-// each length present in a batch; items of requests with another length are
-// skipped.  The longer transforms have kernels of their own (below).
+// The one-piece kernels are instantiated per transform length P <= 4096 (LDS
+// sized by P, so smaller transforms share a CU) and launched once for each
+// length present in a batch; items of requests with another length, or in
+// rows, are skipped.
 
 // The chip floor(n 1023000 / fs) of sample n < N, fs = 1000 N: floor(1023 n / N),
 // in 32 bits (below 2^24) and already below 1023.
@@ -2619,7 +2625,7 @@ __global__ __launch_bounds__(kGenThreads) void k_gen_spec(const ReqDesc *__restr
     }
 }
 
-// One correlation item of length P <= 2048 (see k_gen_corr).
+// One correlation item in one piece, P <= 4096 (see k_gen_corr).
 template <int P>
 __device__ __forceinline__ void gen_corr_item(const ReqDesc &d, int k, int pi, const float2 *tw, const float2 *gen,
                                               float2 *x, float2 *s_tw)
@@ -2691,7 +2697,7 @@ __device__ __forceinline__ void gen_corr_item(const ReqDesc &d, int k, int pi, c
     }
 }
 
-// Correlation of a general-rate request with P <= 2048: item =
+// Correlation of a general-rate request in one piece, P <= 4096: item =
 // (request, Doppler bin, PRN), Doppler-major so that the workgroups running
 // together share the block spectra; over the blocks, Z = X conj(CC) (summed
 // over the segments), the inverse transform and |.|^2 of the lags' outputs,
@@ -2773,7 +2779,8 @@ struct RowFft {
     static constexpr int C = 32 / R;                // columns b per thread
     static constexpr int T = 64 * R;                // threads of a transform
     static constexpr int kGroups = gen_group(P);    // transforms per correlation workgroup
-    static constexpr int kSegRows = (P / 3 + 2047) / 2048;  // rows a segment's samples reach
+    // rows a segment's samples reach: at most (P + 1) / 3 of them (N + ceil(N/2) <= P)
+    static constexpr int kSegRows = ((P + 1) / 3 + 2047) / 2048;
     static_assert(P >= kRowMin && P <= kGenLds && R * C == 32, "four-step lengths");
 };
 
@@ -3060,7 +3067,7 @@ __global__ __launch_bounds__(RowFft<P>::T) void k_gen_spec_rows(const ReqDesc *_
 #pragma unroll
                     for (int a = 0; a < F::R; ++a) f[j][a] = a < NA ? g[j][a < NA ? a : 0] : make_float2(0.f, 0.f);
             };
-            if (d.gen_seg)  // a segment has at most P/3 samples: rows a >= NS are zero
+            if (d.gen_seg)  // rows a >= NS are zero
                 fold(std::integral_constant<int, NS>());
             else if (2 * N <= P)  // M = P
                 fold(std::integral_constant<int, F::R / 2>());
@@ -3494,7 +3501,8 @@ static unsigned grid_for(long long work, long long cap, bool persistent)
 }
 
 // The wipe + fold + boxcar + polyphase stage of a staged batch alone, launched
-// exactly as launch_batch launches it (stage entry point).
+// exactly as launch_batch launches it in the FP16 modes (stage entry point; an FP32
+// search runs the same front end inside k_box_fft).
 hipError_t launch_box(const Launch &L, const uint32_t *d_lut, int2 *d_F, int n_cu, hipStream_t s)
 {
     hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, s, L.hdr);
