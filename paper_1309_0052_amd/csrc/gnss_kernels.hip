@@ -916,7 +916,7 @@ __device__ __forceinline__ void add_group(float (&acc)[PT][16], const ReqDesc &d
 // with the sums in registers.  W waves per workgroup, WPE the waves per SIMD
 // the registers are budgeted for (PRN tile 1 at three waves per SIMD: 165
 // VGPRs; tiles 2 and 4 at two).
-// Bound: vector issue (943 vector instructions per transform, one per 1.8 ns and
+// Bound: vector issue (925 vector instructions per transform, one per 1.8 ns and
 // SIMD; LDS carries 74 KB per transform, three quarters of its rate).  On the
 // weak-signal search (32 PRNs x 121 bins x 25 blocks x 16 phases, 1.55 million
 // transforms) 2.55-2.75 ms, against 3.15-3.3 for one 2048-point transform per
@@ -1723,7 +1723,8 @@ static_assert(kCorrWavesX * 16 * kCol0Row <= 1024 * (kCorrWavesX + 1), "held in 
 // With those gone the waves waited for their spectra, so a wave takes two PRNs per
 // staged spectrum and nothing between one copy and the next waits for memory.  The
 // weak-signal search's correlations (32 PRNs, 121 bins, 25 blocks, 16 phases):
-// 1.11 -> 0.87 ms, with matrix (54%) and vector instructions (46%) back to back.
+// 1.11 -> 0.82 to 0.87 ms, the matrix units busy for 58% of the cycles and the vector
+// instructions, at four clocks each, for 57%.
 template <int NP>
 __device__ __forceinline__ void blocks_x(float (&acc)[NP][2][3][4], const ReqDesc &d, const pfa::u4 *gx, const int *ex,
                                          const pfa::u4 *__restrict__ s_c, pfa::u4 *__restrict__ bufs,
