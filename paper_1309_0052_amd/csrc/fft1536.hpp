@@ -33,7 +33,7 @@ constexpr int kSeg3 = 512;            // samples of a segment (the second one ha
 constexpr int kLen3 = 1536;
 constexpr int kSpec3 = 768;           // float4 per stored segment spectrum
 constexpr int kVec3 = 2 * kSpec3;     // float4 per polyphase vector (two segments)
-// code spectra: the c = 0 and c = 1 thirds only (the code is real, so
+// code spectra (divided by 3): the c = 0 and c = 1 thirds only (the code is real, so
 // X[2][kappa] = conj X[1][-kappa])
 constexpr int kCode3 = 2 * 2 * kSeg3;  // float2 per PRN: [segment][c < 2][kappa]
 // in LDS with a copy of kappa = 0 at kappa = 512 of c = 1 (mirrored reads)

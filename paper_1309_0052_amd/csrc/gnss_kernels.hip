@@ -242,9 +242,14 @@ __global__ __launch_bounds__(256) void k_code_spectra(const uint8_t *codes, cons
         dst[jj * 64 + l] = make_float4(v[2 * jj].x, -v[2 * jj].y, v[2 * jj + 1].x, -v[2 * jj + 1].y);
 }
 
-// FP32 contexts: conj(DFT_1536(cc_i)) of the two segments' replicas (see
+// FP32 contexts: conj(DFT_1536(cc_i)) / 3 of the two segments' replicas (see
 // fft1536.hpp), the c < 2 thirds, [prn][segment][c][kappa], in FP64 and rounded
-// once; row 0 is all zeros.  One thread per value.
+// once; row 0 is all zeros.  One thread per value.  (The third keeps the powers of
+// integer correlations whole multiples of a power of two: with samples of few bits
+// and a carrier at a quarter of the rate the sums over blocks are then exact, as on
+// transforms of 2^k points.  With the factor 9 of an unscaled 1536-point transform in
+// them they round, for equal blocks the same way every time: up to 5e-6 off after
+// 256 blocks.)
 __global__ __launch_bounds__(256) void k_code_spectra3(const uint8_t *codes, float2 *cs)
 {
     __shared__ double2 s_w[kLen3];
@@ -268,7 +273,7 @@ __global__ __launch_bounds__(256) void k_code_spectra3(const uint8_t *codes, flo
         e += k;
         if (e >= kLen3) e -= kLen3;
     }
-    cs[(long long)prn * kCode3 + idx] = make_float2((float)re, (float)im);
+    cs[(long long)prn * kCode3 + idx] = make_float2((float)(re / 3.0), (float)(im / 3.0));
 }
 
 hipError_t launch_code_spectra3(const uint8_t *d_codes, float2 *d_cs, hipStream_t s)
@@ -932,8 +937,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(WPE))) v
     constexpr int kXbBytes = W * kXbuf3 * (int)sizeof(float2);
     constexpr int kStageBytes = PT * 1024 * (W + 1) * (int)sizeof(float);
     constexpr int kSmem = kCcBytes + kXbBytes > kStageBytes ? kCcBytes + kXbBytes : kStageBytes;
-    // 2^-24 (LUT scale) over the square of the unnormalised transform's length
-    constexpr float kScale = (float)(0x1p-24 / ((double)kLen3 * kLen3));
+    // 2^-24 (LUT scale) over the square of the unnormalised transform's length and of
+    // the code spectra's third
+    constexpr float kScale = (float)(0x1p-24 * 9.0 / ((double)kLen3 * kLen3));
     __shared__ __align__(16) unsigned char smem[kSmem];
     __shared__ long long s_item;
     float2 *s_cc = (float2 *)smem;
